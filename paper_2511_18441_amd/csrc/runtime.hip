@@ -525,7 +525,6 @@ recogs_status recogs_select(const recogs_scene *scene, const recogs_camera *cam,
     if ((s = check_scene(scene)) != RECOGS_OK) return s;
     if ((s = check_camera(cam)) != RECOGS_OK) return s;
     if (!params || !count || (scene->n > 0 && !mask)) return fail(RECOGS_ERR_INVALID, "params / mask / count is NULL");
-    launch_fill_u32((uint32_t *)count, 0u, 1, stream);
     launch_select(scene->storage, make_scene(*scene), make_cam(*cam, 16, 16), *params, mask, count, stream);
     return hip_check("select");
 }
