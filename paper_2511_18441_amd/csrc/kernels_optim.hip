@@ -122,106 +122,149 @@ void launch_adam(float *p, const float *g, float *m, float *v, int64_t count, fl
 // are separable blurs; S = (2 mu_y mu_t + C1)(2 s_yt + C2) / ((mu_y^2 + mu_t^2 + C1)
 // (s_y^2 + s_t^2 + C2)). Its gradient: S depends on y through mu_y = G*y, E_yy = G*(y^2)
 // and E_yt = G*(y t), so dS/dy = G*a + 2 y (G*b) + t (G*c) with a, b, c the partial
-// derivatives of S in those maps. Two passes over 16 x 16 output tiles, each with its
-// 26 x 26 input halo in LDS, blurred along x then along y:
-//   k_ssim_fwd: a workgroup per (tile, channel): the three maps a, b, c per pixel and
-//               the tile's sum of S;
-//   k_ssim_bwd: a workgroup per tile, the channels in turn: the blurs of a, b, c and the
-//               gradient; its first workgroup first adds the tiles' sums in a fixed
-//               order (the loss).
+// derivatives of S in those maps. Two passes:
+//   k_ssim_fwd: the three maps a, b, c per value and each workgroup's sum of S;
+//   k_ssim_bwd: the blurs of a, b, c and the gradient; its first workgroup first adds
+//               the workgroups' sums in a fixed order (the loss).
+// Bound by the vector units (about 140 operations per value in the forward, 80 in the
+// backward) and by LDS reads beside them. The three channels are one image of 3 W floats
+// per row whose x taps are 3 apart, so every access is a run of consecutive floats (the
+// maps are stored the same way). A workgroup takes 64 pixels x 8 rows: each thread first
+// blurs one column (of 222: the tile's 192 floats and 15 on either side) down the rows
+// from registers, straight from memory (18 rows for 8: the halo costs loads only), then
+// the blurred rows go through LDS, one 16-byte read per tap for all the blurred
+// quantities, for the blur along x. S needs s_y^2 + s_t^2 only as a sum, so four
+// quantities are blurred (y, t, y^2 + t^2, y t). Tiles are numbered so that one XCD's
+// workgroups take a band of rows, whose halos then meet in its L2. Both passes at
+// 1920x1080: 150 -> 69 us against a workgroup per 16 x 16 tile and channel, blurred
+// along x first with one output and 77 LDS reads per thread (at 1280x720: 78 -> 42 us).
 // ---------------------------------------------------------------------------
 namespace {
 constexpr int kSsimR = 5;                     // window radius (11 taps)
-constexpr int kSsimT = 16;                    // output tile edge
-constexpr int kSsimH = kSsimT + 2 * kSsimR;   // halo tile edge (26)
+constexpr int kSsimTaps = 2 * kSsimR + 1;
+constexpr int kSsimPx = 64;                   // pixels of a workgroup's tile along x
+constexpr int kSsimCols = 3 * kSsimPx;        // its floats along x
+constexpr int kSsimExt = kSsimCols + 6 * kSsimR;   // with the halo (222 <= 256 threads)
+constexpr int kSsimRows = 8;                  // its rows
+constexpr int kSsimIn = kSsimRows + 2 * kSsimR;    // rows read
+constexpr int kSsimRounds = kSsimCols * kSsimRows / 256;   // values per thread of the blur along x
+static_assert(kSsimExt <= 256 && kSsimCols * kSsimRows % 256 == 0, "one thread per column, whole rounds along x");
 constexpr float kSsimC1 = 0.01f * 0.01f, kSsimC2 = 0.03f * 0.03f;
 }  // namespace
 
-struct SsimWindow { float g[2 * kSsimR + 1]; };
+struct SsimWindow { float g[kSsimTaps]; };
+// the order of a blur's taps: the outer, small weights first, so that the running sum (and
+// its rounding) stays small until the last few
+__device__ constexpr int ssim_tap(int i) { return i & 1 ? kSsimTaps - 1 - i / 2 : i / 2; }
 
-// part_l1 (optional): also the tile's sum of |y - t| for the channel (the L1 term)
+// tile (tx, ty) of workgroup b of a grid of 8 * per workgroups (workgroup b runs on XCD
+// b mod 8, which takes tiles [per x, per x + per) in row order); false past the last tile
+__device__ __forceinline__ bool ssim_tile(uint32_t b, uint32_t per, uint32_t gx, uint32_t tiles, uint32_t &tile, int &px0,
+                                          int &row0) {
+    tile = (b & 7u) * per + (b >> 3);
+    if (tile >= tiles) return false;
+    px0 = (int)(tile % gx) * kSsimPx;
+    row0 = (int)(tile / gx) * kSsimRows;
+    return true;
+}
+
+// part_l1 (optional): also the tile's sum of |y - t| (the L1 term)
 __global__ __launch_bounds__(256) void k_ssim_fwd(const float *__restrict__ y, const float *__restrict__ t, int W, int H,
                                                   SsimWindow win, float *__restrict__ maps, float *__restrict__ part,
-                                                  float *__restrict__ part_l1) {
-    __shared__ float s_y[kSsimH * kSsimH], s_t[kSsimH * kSsimH];
-    __shared__ float s_h[5][kSsimH][kSsimT];   // x-blurred y, t, y^2, t^2, y t
+                                                  float *__restrict__ part_l1, uint32_t gx, uint32_t tiles, uint32_t per) {
+    __shared__ float4 s_v[kSsimRows][kSsimExt];   // blurred along y: y, t, y^2 + t^2, y t
     __shared__ float s_w[4], s_w1[4];
-    const int c = blockIdx.z;   // the channel: one workgroup per (tile, channel)
-    const int ox = blockIdx.x * kSsimT, oy = blockIdx.y * kSsimT;
-    const int tx = threadIdx.x % kSsimT, ty = threadIdx.x / kSsimT;
-    const int px = ox + tx, py = oy + ty;
-    const int64_t HW = (int64_t)W * H;
-    // the channel's halo tiles of both images (zero outside the image); every load of the
-    // thread is issued before the first LDS store, so the tile costs one memory round trip
-    constexpr int NL = (kSsimH * kSsimH + 255) / 256;
-    float ly[NL], lt[NL];
+    uint32_t tile;
+    int px0, row0;
+    if (!ssim_tile(blockIdx.x, per, gx, tiles, tile, px0, row0)) return;
+    const int tid = (int)threadIdx.x;
+    const int64_t RW = 3 * (int64_t)W, HW3 = RW * H;
+    float asum = 0.f, ssum = 0.f;
+    if (tid < kSsimExt) {
+        const int64_t e = 3 * (int64_t)px0 - 3 * kSsimR + tid;
+        const bool col = e >= 0 && e < RW;
+        float u[kSsimIn], v[kSsimIn];
 #pragma unroll
-    for (int i = 0; i < NL; ++i) {
-        const int k = (int)threadIdx.x + 256 * i;
-        const int x = ox + k % kSsimH - kSsimR, yy = oy + k / kSsimH - kSsimR;
-        const bool in = k < kSsimH * kSsimH && x >= 0 && x < W && yy >= 0 && yy < H;
-        const int64_t q = in ? ((int64_t)yy * W + x) * 3 + c : 0;
-        ly[i] = in ? y[q] : 0.f;
-        lt[i] = in ? t[q] : 0.f;
-    }
+        for (int r = 0; r < kSsimIn; ++r) {   // (every load unconditional: value 0 stands in outside)
+            const int yy = row0 + r - kSsimR;
+            const int64_t q = col && yy >= 0 && yy < H ? yy * RW + e : 0;
+            u[r] = y[q];
+            v[r] = t[q];
+        }
 #pragma unroll
-    for (int i = 0; i < NL; ++i) {
-        const int k = (int)threadIdx.x + 256 * i;
-        if (k < kSsimH * kSsimH) {
-            s_y[k] = ly[i];
-            s_t[k] = lt[i];
+        for (int r = 0; r < kSsimIn; ++r) {   // zero outside the image
+            const int yy = row0 + r - kSsimR;
+            const bool in = col && yy >= 0 && yy < H;
+            u[r] = in ? u[r] : 0.f;
+            v[r] = in ? v[r] : 0.f;
+        }
+        if (part_l1 && tid >= 3 * kSsimR && tid < 3 * kSsimR + kSsimCols) {
+#pragma unroll
+            for (int o = 0; o < kSsimRows; ++o) asum += fabsf(u[o + kSsimR] - v[o + kSsimR]);   // 0 outside
+        }
+        float s2[kSsimIn], p[kSsimIn];
+#pragma unroll
+        for (int r = 0; r < kSsimIn; ++r) {
+            s2[r] = u[r] * u[r] + v[r] * v[r];
+            p[r] = u[r] * v[r];
+        }
+#pragma unroll
+        for (int o = 0; o < kSsimRows; ++o) {
+            float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int i = 0; i < kSsimTaps; ++i) {
+                const int j = ssim_tap(i);
+                const float g = win.g[j];
+                a.x += g * u[o + j]; a.y += g * v[o + j]; a.z += g * s2[o + j]; a.w += g * p[o + j];
+            }
+            s_v[o][tid] = a;
         }
     }
     __syncthreads();
-    for (int k = threadIdx.x; k < kSsimH * kSsimT; k += 256) {
-        const int r = k / kSsimT, cx = k % kSsimT;
-        float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f, a4 = 0.f;
+#pragma unroll 2
+    for (int i = 0; i < kSsimRounds; ++i) {
+        const int k = tid + 256 * i, o = k / kSsimCols, x = k % kSsimCols;
+        const int64_t e = 3 * (int64_t)px0 + x;
+        const int yy = row0 + o;
+        float my = 0.f, mt = 0.f, e2 = 0.f, eyt = 0.f;
 #pragma unroll
-        for (int j = 0; j <= 2 * kSsimR; ++j) {
-            const float u = s_y[r * kSsimH + cx + j], v = s_t[r * kSsimH + cx + j], g = win.g[j];
-            a0 += g * u; a1 += g * v; a2 += g * (u * u); a3 += g * (v * v); a4 += g * (u * v);
+        for (int n = 0; n < kSsimTaps; ++n) {
+            const int j = ssim_tap(n);
+            const float4 a = s_v[o][x + 3 * j];
+            const float g = win.g[j];
+            my += g * a.x; mt += g * a.y; e2 += g * a.z; eyt += g * a.w;
         }
-        s_h[0][r][cx] = a0; s_h[1][r][cx] = a1; s_h[2][r][cx] = a2; s_h[3][r][cx] = a3; s_h[4][r][cx] = a4;
-    }
-    __syncthreads();
-    float my = 0.f, mt = 0.f, eyy = 0.f, ett = 0.f, eyt = 0.f;
-#pragma unroll
-    for (int j = 0; j <= 2 * kSsimR; ++j) {
-        const float g = win.g[j];
-        my += g * s_h[0][ty + j][tx]; mt += g * s_h[1][ty + j][tx];
-        eyy += g * s_h[2][ty + j][tx]; ett += g * s_h[3][ty + j][tx]; eyt += g * s_h[4][ty + j][tx];
-    }
-    float ssum = 0.f, asum = 0.f;
-    if (part_l1 && px < W && py < H) {
-        const int k = (ty + kSsimR) * kSsimH + tx + kSsimR;
-        asum = fabsf(s_y[k] - s_t[k]);
-    }
-    if (px < W && py < H) {
-        const float syy = eyy - my * my, stt = ett - mt * mt, syt = eyt - my * mt;
-        const float l1 = 2.f * my * mt + kSsimC1, l2 = my * my + mt * mt + kSsimC1;
-        const float c1 = 2.f * syt + kSsimC2, c2 = syy + stt + kSsimC2;
-        const float il2c2 = 1.f / (l2 * c2);
-        const float S = l1 * c1 * il2c2;
-        const float dS_dsyt = 2.f * l1 * il2c2;
-        const float dS_dsyy = -S / c2;
-        const float dS_dmy = 2.f * mt * c1 * il2c2 - S * 2.f * my / l2;
-        const int64_t p = (int64_t)py * W + px;
-        maps[(3 * c + 0) * HW + p] = dS_dmy - 2.f * my * dS_dsyy - mt * dS_dsyt;   // a
-        maps[(3 * c + 1) * HW + p] = dS_dsyy;                                    // b
-        maps[(3 * c + 2) * HW + p] = dS_dsyt;                                    // c
-        ssum = S;
+        if (e < RW && yy < H) {
+            const float syt = __builtin_fmaf(-my, mt, eyt);
+            const float s2 = __builtin_fmaf(-mt, mt, __builtin_fmaf(-my, my, e2));
+            const float l1 = 2.f * my * mt + kSsimC1, l2 = my * my + mt * mt + kSsimC1;
+            const float c1 = 2.f * syt + kSsimC2, c2 = s2 + kSsimC2;
+            // 1 / (l2 c2): the hardware reciprocal and one Newton step (kept out where it
+            // is not finite: den zero or infinite)
+            const float den = l2 * c2, rc = __builtin_amdgcn_rcpf(den);
+            const float nr = __builtin_fmaf(__builtin_fmaf(-den, rc, 1.f), rc, rc);
+            const float inv = __builtin_isfinite(nr) ? nr : rc;
+            const float S = l1 * c1 * inv;
+            const float dS_dsyt = 2.f * l1 * inv;
+            const float dS_dsyy = -S * (l2 * inv);
+            const float dS_dmy = 2.f * mt * c1 * inv - S * 2.f * my * (c2 * inv);
+            const int64_t q = yy * RW + e;
+            maps[q] = dS_dmy - 2.f * my * dS_dsyy - mt * dS_dsyt;   // a
+            maps[HW3 + q] = dS_dsyy;                                // b
+            maps[2 * HW3 + q] = dS_dsyt;                            // c
+            ssum += S;
+        }
     }
     ssum = wave_sum(ssum);
-    if (lane_id() == 0) s_w[threadIdx.x >> 6] = ssum;
+    if (lane_id() == 0) s_w[tid >> 6] = ssum;
     if (part_l1) {
         asum = wave_sum(asum);
-        if (lane_id() == 0) s_w1[threadIdx.x >> 6] = asum;
+        if (lane_id() == 0) s_w1[tid >> 6] = asum;
     }
     __syncthreads();
     // the workgroup's sums, added to the others in a fixed order by the backward
-    const size_t at = ((size_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-    if (threadIdx.x == 0) part[at] = ((s_w[0] + s_w[1]) + s_w[2]) + s_w[3];
-    if (part_l1 && threadIdx.x == 0) part_l1[at] = ((s_w1[0] + s_w1[1]) + s_w1[2]) + s_w1[3];
+    if (tid == 0) part[tile] = ((s_w[0] + s_w[1]) + s_w[2]) + s_w[3];
+    if (part_l1 && tid == 0) part_l1[tile] = ((s_w1[0] + s_w1[1]) + s_w1[2]) + s_w1[3];
 }
 
 // The n partial sums added in a fixed order by one workgroup (thread t: entries t,
@@ -243,93 +286,101 @@ __device__ __forceinline__ float fixed_order_sum(const float *__restrict__ part,
     return ((s_w[0] + s_w[1]) + s_w[2]) + s_w[3];
 }
 
+// One gradient value from its SSIM term d: after the L1 term (l1_scale sign(diff)), or the
+// stored value with accumulate, in this order and with no fused multiply-add, so that both
+// terms in one call have the bits of the two calls.
+__device__ __forceinline__ float ssim_grad(float d, bool with_l1, float l1_scale, float diff, int accumulate, const float *prev) {
+#pragma clang fp contract(off)
+    if (with_l1) d = l1_scale * sgn(diff) + d;
+    return accumulate ? *prev + d : d;
+}
+
 // part / nparts / weight / loss: the loss weight + gscale (sum of S), plus l1_scale (sum
-// of |y - t|) with part_l1, summed by workgroup (0, 0) before its tile. With part_l1 the
+// of |y - t|) with part_l1, summed by workgroup 0 before its tile. With part_l1 the
 // gradient also takes l1_scale sign(y - t), added before the SSIM term is (the bits of
 // the L1 gradient written first and the SSIM gradient added to it).
 __global__ __launch_bounds__(256) void k_ssim_bwd(const float *__restrict__ y, const float *__restrict__ t, int W, int H,
                                                   SsimWindow win, const float *__restrict__ maps, float gscale,
                                                   int accumulate, float *__restrict__ dldy, const float *__restrict__ part,
                                                   uint32_t nparts, float weight, float *__restrict__ loss,
-                                                  const float *__restrict__ part_l1, float l1_scale) {
-    __shared__ float s_m[3][kSsimH * kSsimH];
-    __shared__ float s_h[3][kSsimH][kSsimT];
+                                                  const float *__restrict__ part_l1, float l1_scale, uint32_t gx,
+                                                  uint32_t tiles, uint32_t per) {
+    __shared__ float2 s_ab[kSsimRows][kSsimExt];   // a, b blurred along y
+    __shared__ float s_c[kSsimRows][kSsimExt];     // c
     __shared__ float s_lw[4], s_lw1[4];
-    if (blockIdx.x == 0 && blockIdx.y == 0) {
+    const int tid = (int)threadIdx.x;
+    if (blockIdx.x == 0) {
         const float ss = fixed_order_sum(part, nparts, s_lw);
         if (part_l1) {
             const float sa = fixed_order_sum(part_l1, nparts, s_lw1);
-            if (threadIdx.x == 0) *loss = (weight + gscale * ss) + l1_scale * sa;
-        } else if (threadIdx.x == 0) {
+            if (tid == 0) *loss = (weight + gscale * ss) + l1_scale * sa;
+        } else if (tid == 0) {
             *loss = weight + gscale * ss;
         }
     }
-    const int ox = blockIdx.x * kSsimT, oy = blockIdx.y * kSsimT;
-    const int tx = threadIdx.x % kSsimT, ty = threadIdx.x / kSsimT;
-    const int px = ox + tx, py = oy + ty;
-    const int64_t HW = (int64_t)W * H;
-    // The three channels in turn (a pixel's three gradient values are then written by one
-    // workgroup); the three maps of channel c + 1 are loaded into registers while channel
-    // c is blurred, so the loads after the first channel's are off the critical path.
-    constexpr int NL = (kSsimH * kSsimH + 255) / 256;
-    float lm[3][NL];
-    int64_t lp[NL];
+    uint32_t tile;
+    int px0, row0;
+    if (!ssim_tile(blockIdx.x, per, gx, tiles, tile, px0, row0)) return;
+    const int64_t RW = 3 * (int64_t)W, HW3 = RW * H;
+    if (tid < kSsimExt) {
+        const int64_t e = 3 * (int64_t)px0 - 3 * kSsimR + tid;
+        const bool col = e >= 0 && e < RW;
+        float m[3][kSsimIn];
 #pragma unroll
-    for (int i = 0; i < NL; ++i) {
-        const int k = (int)threadIdx.x + 256 * i;
-        const int x = ox + k % kSsimH - kSsimR, yy = oy + k / kSsimH - kSsimR;
-        lp[i] = (k < kSsimH * kSsimH && x >= 0 && x < W && yy >= 0 && yy < H) ? (int64_t)yy * W + x : -1;
-    }
-    auto load_maps = [&](int c) {
+        for (int r = 0; r < kSsimIn; ++r) {
+            const int yy = row0 + r - kSsimR;
+            const int64_t q = col && yy >= 0 && yy < H ? yy * RW + e : 0;
 #pragma unroll
-        for (int q = 0; q < 3; ++q)
-#pragma unroll
-            for (int i = 0; i < NL; ++i) lm[q][i] = lp[i] >= 0 ? maps[(3 * c + q) * HW + lp[i]] : 0.f;
-    };
-    load_maps(0);
-    for (int c = 0; c < 3; ++c) {
-        __syncthreads();   // the previous channel's reads of s_m and s_h done
-#pragma unroll
-        for (int q = 0; q < 3; ++q)
-#pragma unroll
-            for (int i = 0; i < NL; ++i) {
-                const int k = (int)threadIdx.x + 256 * i;
-                if (k < kSsimH * kSsimH) s_m[q][k] = lm[q][i];
-            }
-        __syncthreads();
-        if (c < 2) load_maps(c + 1);
-        for (int k = threadIdx.x; k < kSsimH * kSsimT; k += 256) {
-            const int r = k / kSsimT, cx = k % kSsimT;
-            float a0 = 0.f, a1 = 0.f, a2 = 0.f;
-#pragma unroll
-            for (int j = 0; j <= 2 * kSsimR; ++j) {
-                const float g = win.g[j];
-                a0 += g * s_m[0][r * kSsimH + cx + j]; a1 += g * s_m[1][r * kSsimH + cx + j]; a2 += g * s_m[2][r * kSsimH + cx + j];
-            }
-            s_h[0][r][cx] = a0; s_h[1][r][cx] = a1; s_h[2][r][cx] = a2;
+            for (int k = 0; k < 3; ++k) m[k][r] = maps[k * HW3 + q];
         }
-        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kSsimIn; ++r) {
+            const int yy = row0 + r - kSsimR;
+            const bool in = col && yy >= 0 && yy < H;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) m[k][r] = in ? m[k][r] : 0.f;
+        }
+#pragma unroll
+        for (int o = 0; o < kSsimRows; ++o) {
+            float a = 0.f, b = 0.f, c = 0.f;
+#pragma unroll
+            for (int i = 0; i < kSsimTaps; ++i) {
+                const int j = ssim_tap(i);
+                const float g = win.g[j];
+                a += g * m[0][o + j]; b += g * m[1][o + j]; c += g * m[2][o + j];
+            }
+            s_ab[o][tid] = make_float2(a, b);
+            s_c[o][tid] = c;
+        }
+    }
+    __syncthreads();
+#pragma unroll 2
+    for (int i = 0; i < kSsimRounds; ++i) {
+        const int k = tid + 256 * i, o = k / kSsimCols, x = k % kSsimCols;
+        const int64_t e = 3 * (int64_t)px0 + x;
+        const int yy = row0 + o;
+        const bool in = e < RW && yy < H;
+        const int64_t q = in ? yy * RW + e : 0;
+        const float yp = in ? y[q] : 0.f, tp = in ? t[q] : 0.f;
         float ga = 0.f, gb = 0.f, gc = 0.f;
 #pragma unroll
-        for (int j = 0; j <= 2 * kSsimR; ++j) {
+        for (int n = 0; n < kSsimTaps; ++n) {
+            const int j = ssim_tap(n);
+            const float2 ab = s_ab[o][x + 3 * j];
             const float g = win.g[j];
-            ga += g * s_h[0][ty + j][tx]; gb += g * s_h[1][ty + j][tx]; gc += g * s_h[2][ty + j][tx];
+            ga += g * ab.x; gb += g * ab.y; gc += g * s_c[o][x + 3 * j];
         }
-        if (px < W && py < H) {
-            const int64_t p = ((int64_t)py * W + px) * 3 + c;
-            const float yp = y[p], tp = t[p];
-            float d = gscale * (ga + 2.f * yp * gb + tp * gc);
-            if (part_l1) d = l1_scale * sgn(yp - tp) + d;
-            dldy[p] = accumulate ? dldy[p] + d : d;
-        }
+        if (in) dldy[q] = ssim_grad(gscale * (ga + 2.f * yp * gb + tp * gc), part_l1 != nullptr, l1_scale, yp - tp, accumulate,
+                                    dldy + q);
     }
 }
 
-// Scratch floats of the SSIM term: 9 per pixel (the maps), then two per (16 x 16 tile,
-// channel) (the partial sums of S, then those of |y - t|).
+// Scratch floats of the SSIM term: 9 per pixel (the maps), then 6 per 16 x 16 tile of the
+// image, which hold the workgroups' partial sums of S and of |y - t|: two per 64 x 8 tile
+// (at most two such tiles per 16 x 16 one, where the image is narrow).
 size_t dssim_scratch_floats(int W, int H) {
     if (W <= 0 || H <= 0) return 0;
-    const size_t tiles = (size_t)((W + kSsimT - 1) / kSsimT) * (size_t)((H + kSsimT - 1) / kSsimT);
+    const size_t tiles = (size_t)((W + 15) / 16) * (size_t)((H + 15) / 16);
     return (size_t)9 * (size_t)W * (size_t)H + 6 * tiles;
 }
 
@@ -353,13 +404,13 @@ void launch_dssim(const float *y, const float *t, int W, int H, float weight, fl
         return;
     }
     const double N = 3.0 * (double)W * (double)H;
-    const dim3 grid((unsigned)((W + kSsimT - 1) / kSsimT), (unsigned)((H + kSsimT - 1) / kSsimT), 3u);
-    const uint32_t nparts = grid.x * grid.y * grid.z;
+    const uint32_t gx = (uint32_t)((W + kSsimPx - 1) / kSsimPx), gy = (uint32_t)((H + kSsimRows - 1) / kSsimRows);
+    const uint32_t tiles = gx * gy, per = (tiles + 7u) / 8u;
     float *part = maps + (size_t)9 * (size_t)W * (size_t)H;
-    float *part_l1 = with_l1 ? part + nparts : nullptr;
-    hipLaunchKernelGGL(k_ssim_fwd, grid, dim3(256), 0, st, y, t, W, H, win, maps, part, part_l1);
-    hipLaunchKernelGGL(k_ssim_bwd, dim3(grid.x, grid.y), dim3(256), 0, st, y, t, W, H, win, maps, (float)(-weight / N),
-                       accumulate, dldy, part, nparts, weight, loss, part_l1, l1_scale);
+    float *part_l1 = with_l1 ? part + tiles : nullptr;
+    hipLaunchKernelGGL(k_ssim_fwd, dim3(8u * per), dim3(256), 0, st, y, t, W, H, win, maps, part, part_l1, gx, tiles, per);
+    hipLaunchKernelGGL(k_ssim_bwd, dim3(8u * per), dim3(256), 0, st, y, t, W, H, win, maps, (float)(-weight / N), accumulate,
+                       dldy, part, tiles, weight, loss, part_l1, l1_scale, gx, tiles, per);
 }
 
 }  // namespace recogs
