@@ -23,6 +23,32 @@ namespace recogs {
 
 void launch_fill_u32(uint32_t *p, uint32_t v, int64_t count, hipStream_t st);
 
+// One splat replayed on one pixel: the forward's decisions with its arithmetic (act: the
+// entry is not past the pixel's last blended one; alpha at or above 1/255), the pixel's
+// state advanced, and the pixel's terms of the splat's sums: dr, dg, db and vs = sigma
+// dL/dsigma (0 where alpha is clamped; the factor 1 / sigma of the whole splat is applied
+// to the sum). With alpha taken as 0 where the splat is not blended, x = T s and Gr' = Gr -
+// alpha x, the same three values serve the weight, the state and dL/dalpha = x - Gr' / (1 -
+// alpha): 28 vector instructions (36 with separate selects and products). Only the exponent
+// and T take part in decisions; they have the forward's operations.
+struct BwdPixel { float T, Gr, g0, g1, g2; };
+__device__ __forceinline__ bool bwd_step(BwdPixel &p, ExpRow er, float4 r1, float4 r2, float dy, bool in, float &vs, float &dr,
+                                         float &dg, float &db) {
+    const float e = exp_at(er, r1, dy);
+    const bool act = in && !(e < kLog2AlphaMin);
+    const float araw = __builtin_amdgcn_exp2f(e);
+    const float a = act ? fminf(kAlphaMax, araw) : 0.f;
+    const float x = p.T * __builtin_fmaf(p.g2, r2.z, __builtin_fmaf(p.g1, r2.y, p.g0 * r2.x));
+    const float wgt = a * p.T;
+    p.Gr = __builtin_fmaf(-a, x, p.Gr);
+    // (finite: 1 - a >= 0.01)
+    const float dal = __builtin_fmaf(-p.Gr, __builtin_amdgcn_rcpf(1.f - a), x);
+    vs = dal * ((act && araw < kAlphaMax) ? araw : 0.f);
+    dr = wgt * p.g0; dg = wgt * p.g1; db = wgt * p.g2;
+    p.T = __builtin_fmaf(-a, p.T, p.T);   // T (1 - alpha), rounded once; T itself at alpha 0
+    return act;
+}
+
 template <int TW, int TH, int PPT>
 __global__ __launch_bounds__(TW *TH / PPT) void k_blend_bwd(const uint2 *__restrict__ ranges, const uint32_t *__restrict__ vals,
                                                            const SplatRec *__restrict__ rec, const uint2 *__restrict__ rect,
@@ -40,7 +66,8 @@ __global__ __launch_bounds__(TW *TH / PPT) void k_blend_bwd(const uint2 *__restr
     constexpr int BATCH = NT >= 256 ? 256 : kBlendBatch;
     struct Stage { BlendRec r[BATCH]; };
     __shared__ Stage sm;   // BlendRec.pad holds the (Gaussian, tile) slot, rgb.w the opacity
-    __shared__ float4 s_acc[NW][BATCH];
+    __shared__ float4 s_acc[NW][BATCH];          // the waves' sums, where s_wrote has the record's bit
+    __shared__ uint64_t s_wrote[NW][BATCH / 64];
     const int tile = blockIdx.x;
     const uint32_t tcx = (uint32_t)(tile % tiles_x), tcy = (uint32_t)(tile / tiles_x);
     const int tx0 = (int)tcx * TW, ty0 = (int)tcy * TH;
@@ -55,20 +82,20 @@ __global__ __launch_bounds__(TW *TH / PPT) void k_blend_bwd(const uint2 *__restr
     // Gr = g . (y - A) (the g-weighted colour not yet accounted for, starting at g . y),
     // g . R_i = Gr - alpha_i T_i s_i, so dL/dalpha_i = T_i s_i - (Gr - alpha_i T_i s_i) / (1 - alpha_i)
     // and Gr decreases by alpha_i T_i s_i after splat i.
-    float pyc[PPT], T[PPT], Gr[PPT], g0[PPT], g1[PPT], g2[PPT];
+    float pyc[PPT];
+    BwdPixel P[PPT];
     uint32_t np[PPT];
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
         const int py = ty0 + lrow * PPT + j;
         pyc[j] = (float)py + 0.5f;
-        T[j] = 1.f;
         np[j] = 0;
-        Gr[j] = g0[j] = g1[j] = g2[j] = 0.f;
+        P[j] = BwdPixel{1.f, 0.f, 0.f, 0.f, 0.f};
         if (px < W && py < H) {
             const int64_t p = (int64_t)py * W + px;
             np[j] = nproc[p];
-            g0[j] = dldy[p * 3]; g1[j] = dldy[p * 3 + 1]; g2[j] = dldy[p * 3 + 2];
-            Gr[j] = g0[j] * image[p * 3] + g1[j] * image[p * 3 + 1] + g2[j] * image[p * 3 + 2];
+            P[j].g0 = dldy[p * 3]; P[j].g1 = dldy[p * 3 + 1]; P[j].g2 = dldy[p * 3 + 2];
+            P[j].Gr = P[j].g0 * image[p * 3] + P[j].g1 * image[p * 3 + 1] + P[j].g2 * image[p * 3 + 2];
         }
     }
     uint32_t npmax = 0;
@@ -112,11 +139,7 @@ __global__ __launch_bounds__(TW *TH / PPT) void k_blend_bwd(const uint2 *__restr
     for (uint32_t start = rg.x; start < rg.y; start += BATCH) {
         if (__syncthreads_and(start - rg.x >= npmax)) break;
         if constexpr (PIPE) {
-            if (t < BATCH) {
-                if (start + (uint32_t)t < rg.y) stage(t, f0, f1, f2, frc, fko);
-#pragma unroll
-                for (int ww = 0; ww < NW; ++ww) s_acc[ww][t] = make_float4(0.f, 0.f, 0.f, 0.f);
-            }
+            if (t < BATCH && start + (uint32_t)t < rg.y) stage(t, f0, f1, f2, frc, fko);
         } else {
             for (int q = t; q < BATCH; q += NT) {
                 const uint32_t k = start + q;
@@ -125,8 +148,6 @@ __global__ __launch_bounds__(TW *TH / PPT) void k_blend_bwd(const uint2 *__restr
                     const SplatRec sp = rec[gid];
                     stage(q, sp.r0, sp.r1, sp.r2, rect[gid], koff[gid]);
                 }
-#pragma unroll
-                for (int ww = 0; ww < NW; ++ww) s_acc[ww][q] = make_float4(0.f, 0.f, 0.f, 0.f);
             }
         }
         __syncthreads();
@@ -148,8 +169,9 @@ __global__ __launch_bounds__(TW *TH / PPT) void k_blend_bwd(const uint2 *__restr
         bool quit = false;
 #pragma unroll
         for (int c = 0; c < BATCH / 64; ++c) {
-            uint64_t mm = todo[c];
+            uint64_t mm = todo[c], wrote = 0;
             while (mm && !quit) {
+                const uint64_t bit = mm & (0ull - mm);
                 const int q = c * 64 + (int)__builtin_ctzll(mm);
                 mm &= mm - 1;
                 const uint32_t krel = start + q - rg.x;
@@ -161,59 +183,49 @@ __global__ __launch_bounds__(TW *TH / PPT) void k_blend_bwd(const uint2 *__restr
                 }
                 const float4 *br = reinterpret_cast<const float4 *>(&sm.r[q]);
                 const float4 h = br[0], r1 = br[1], r2 = br[2];
-                const float2 uv = make_float2(h.x, h.y);
-                // 1 / sigma to about 1 ulp: it only scales this splat's opacity gradient
-                float inv_sigma = __builtin_amdgcn_rcpf(r2.w);
-                // here, not sunk into the branch below: the record's last 16 bytes then
-                // come in one LDS read with the rest, not a second read and wait
-                asm volatile("" : "+v"(inv_sigma));
-                const ExpRow er = exp_row(r1, pxc - uv.x);
+                const ExpRow er = exp_row(r1, pxc - h.x);
                 float ds, dr, dg, db;
                 bool any = false;
 #pragma unroll
                 for (int j = 0; j < PPT; ++j) {
-                    // the forward's decisions, replayed with its arithmetic: entries up to
-                    // the pixel's last blended one, alpha at or above 1/255
-                    const float e = exp_at(er, r1, pyc[j] - uv.y);
-                    const bool act = krel < np[j] && !(e < kLog2AlphaMin);
-                    any = any || act;
-                    const float araw = __builtin_amdgcn_exp2f(e);
-                    const float a = fminf(kAlphaMax, araw);
-                    const float wgt = act ? a * T[j] : 0.f;
-                    const float sg = g0[j] * r2.x + g1[j] * r2.y + g2[j] * r2.z;
-                    const float ws = wgt * sg;
-                    // (finite: 1 - a >= 0.01) computed on every lane, selected by a factor
-                    const float dal = T[j] * sg - (Gr[j] - ws) * __builtin_amdgcn_rcpf(1.f - a);
-                    const float vs = dal * ((act && araw < kAlphaMax) ? araw * inv_sigma : 0.f);
+                    float vs, vr, vg, vb;
+                    any |= bwd_step(P[j], er, r1, r2, pyc[j] - h.y, krel < np[j], vs, vr, vg, vb);
                     if (j == 0) {   // (no adds of zero: x + 0 is not folded, for the sign of zero)
-                        dr = wgt * g0[j]; dg = wgt * g1[j]; db = wgt * g2[j]; ds = vs;
+                        ds = vs; dr = vr; dg = vg; db = vb;
                     } else {
-                        dr += wgt * g0[j]; dg += wgt * g1[j]; db += wgt * g2[j]; ds += vs;
+                        ds += vs; dr += vr; dg += vg; db += vb;
                     }
-                    Gr[j] -= ws;
-                    T[j] = act ? __builtin_fmaf(-a, T[j], T[j]) : T[j];
                 }
                 if (wave_ballot(any)) {
+                    wrote |= bit;
                     if constexpr (L == 64) {
                         const float tot = wave_sum4(ds, dr, dg, db);
                         const uint32_t l = lane_id();
-                        if (l < 4) ((float *)&s_acc[wv][q])[sum4_part(l)] = tot;
+                        if (sum4_writes(l)) ((float *)&s_acc[wv][q])[sum4_part(l)] = tot;
                     } else {
                         ds = wave_sum_dpp<L>(ds); dr = wave_sum_dpp<L>(dr); dg = wave_sum_dpp<L>(dg); db = wave_sum_dpp<L>(db);
                         if (lane_id() == 0) s_acc[wv][q] = make_float4(ds, dr, dg, db);
                     }
                 }
             }
+            if (lane_id() == 0) s_wrote[wv][c] = wrote;
         }
         __syncthreads();
         for (int q = t; q < nb; q += NT) {
-            float4 v = s_acc[0][q];
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            bool some = false;
 #pragma unroll
-            for (int ww = 1; ww < NW; ++ww) {
-                const float4 x = s_acc[ww][q];
-                v.x += x.x; v.y += x.y; v.z += x.z; v.w += x.w;
+            for (int ww = 0; ww < NW; ++ww) {
+                if ((s_wrote[ww][q >> 6] >> (q & 63)) & 1ull) {
+                    const float4 x = s_acc[ww][q];
+                    v.x += x.x; v.y += x.y; v.z += x.z; v.w += x.w;
+                    some = true;
+                }
             }
-            if (v.x != 0.f || v.y != 0.f || v.z != 0.f || v.w != 0.f) gk[sm.r[q].pad] = v;
+            if (some) {
+                v.x *= __builtin_amdgcn_rcpf(sm.r[q].rgb.w);   // 1 / sigma to about 1 ulp
+                gk[sm.r[q].pad] = v;
+            }
         }
     }
 }
@@ -253,20 +265,20 @@ __global__ __launch_bounds__((TW / 8) * (TH / (8 * PPT)) * 64) void k_blend_bwd_
     const float pxc = (float)px + 0.5f;
     const float x0 = (float)bx + 0.5f, x1 = x0 + 7.f;
     const float y0 = (float)by + 0.5f, y1 = y0 + (float)(8 * PPT - 1);
-    float pyc[PPT], T[PPT], Gr[PPT], g0[PPT], g1[PPT], g2[PPT];
+    float pyc[PPT];
+    BwdPixel P[PPT];
     uint32_t np[PPT], npl = 0;
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
         const int py = by + (l >> 3) * PPT + j;
         pyc[j] = (float)py + 0.5f;
-        T[j] = 1.f;
         np[j] = 0;
-        Gr[j] = g0[j] = g1[j] = g2[j] = 0.f;
+        P[j] = BwdPixel{1.f, 0.f, 0.f, 0.f, 0.f};
         if (px < W && py < H) {
             const int64_t p = (int64_t)py * W + px;
             np[j] = nproc[p];
-            g0[j] = dldy[p * 3]; g1[j] = dldy[p * 3 + 1]; g2[j] = dldy[p * 3 + 2];
-            Gr[j] = g0[j] * image[p * 3] + g1[j] * image[p * 3 + 1] + g2[j] * image[p * 3 + 2];
+            P[j].g0 = dldy[p * 3]; P[j].g1 = dldy[p * 3 + 1]; P[j].g2 = dldy[p * 3 + 2];
+            P[j].Gr = P[j].g0 * image[p * 3] + P[j].g1 * image[p * 3 + 1] + P[j].g2 * image[p * 3 + 2];
         }
         npl = max(npl, np[j]);
     }
@@ -315,36 +327,24 @@ __global__ __launch_bounds__((TW / 8) * (TH / (8 * PPT)) * 64) void k_blend_bwd_
         for (int q = 0; q < nh; ++q) {
             const float4 h = sm[region][q][0], r1 = sm[region][q][1], r2 = sm[region][q][2];
             const uint32_t krel = __float_as_uint(h.w);
-            const float2 uv = make_float2(h.x, h.y);
-            // 1 / sigma to about 1 ulp: it only scales this splat's opacity gradient
-            const float inv_sigma = __builtin_amdgcn_rcpf(r2.w);
-            const ExpRow er = exp_row(r1, pxc - uv.x);
+            const ExpRow er = exp_row(r1, pxc - h.x);
             float ds, dr, dg, db;
             bool any = false;
 #pragma unroll
             for (int j = 0; j < PPT; ++j) {
-                const float e = exp_at(er, r1, pyc[j] - uv.y);
-                const bool act = krel <= np[j] && !(e < kLog2AlphaMin);
-                any = any || act;
-                const float araw = __builtin_amdgcn_exp2f(e);
-                const float a = fminf(kAlphaMax, araw);
-                const float wgt = act ? a * T[j] : 0.f;
-                const float sg = g0[j] * r2.x + g1[j] * r2.y + g2[j] * r2.z;
-                const float ws = wgt * sg;
-                // (finite: 1 - a >= 0.01) computed on every lane, selected by a factor
-                const float dal = T[j] * sg - (Gr[j] - ws) * __builtin_amdgcn_rcpf(1.f - a);
-                const float vs = dal * ((act && araw < kAlphaMax) ? araw * inv_sigma : 0.f);
+                float vs, vr, vg, vb;
+                any |= bwd_step(P[j], er, r1, r2, pyc[j] - h.y, krel <= np[j], vs, vr, vg, vb);
                 if (j == 0) {   // (no adds of zero: x + 0 is not folded, for the sign of zero)
-                    dr = wgt * g0[j]; dg = wgt * g1[j]; db = wgt * g2[j]; ds = vs;
+                    ds = vs; dr = vr; dg = vg; db = vb;
                 } else {
-                    dr += wgt * g0[j]; dg += wgt * g1[j]; db += wgt * g2[j]; ds += vs;
+                    ds += vs; dr += vr; dg += vg; db += vb;
                 }
-                Gr[j] -= ws;
-                T[j] = act ? __builtin_fmaf(-a, T[j], T[j]) : T[j];
             }
             if (wave_ballot(any)) {
-                const float tot = wave_sum4(ds, dr, dg, db);
-                if (l < 4) ((float *)(wsub + wcount + __builtin_popcountll(wrote)))[sum4_part((uint32_t)l)] = tot;
+                // (1 / sigma to about 1 ulp, on the opacity sum)
+                const float tot = wave_sum4(ds * __builtin_amdgcn_rcpf(r2.w), dr, dg, db);
+                if (sum4_writes((uint32_t)l))
+                    ((float *)(wsub + wcount + __builtin_popcountll(wrote)))[sum4_part((uint32_t)l)] = tot;
                 wrote |= 1ull << q;
             }
         }

@@ -142,33 +142,42 @@ template <int LANES> __device__ __forceinline__ float wave_sum_dpp(float v) {
 }
 
 // Totals of four floats over the 64 lanes of a wave, transposed as they are summed so
-// that each step moves one value per lane: lanes l and l^1 trade halves (even lanes keep
-// a and b, odd lanes c and d), lanes l and l^2 trade again (one value per lane: a, c, b,
-// d in lanes 4m + 0, 1, 2, 3), the four same-value lanes of a row by rotations of 4 and
-// 8 lanes, then the rows by lane exchanges across 16 and 32. Lanes 0..3 return the
-// totals of a, c, b, d (lane l holds value ((l & 1) << 1) | ((l >> 1) & 1) of the
-// four). Every addition has a fixed place, so the totals are the same bits on every run.
+// that each step moves one value per lane. v_permlane32_swap of (x, y) leaves the lower
+// halves of both in one register and the upper halves in the other, so one swap and one
+// add fold x into lanes 0-31 and y into lanes 32-63; v_permlane16_swap does the same with
+// the 16-lane rows; the 16 lanes of a row are then added by rotations. Ten vector
+// instructions, no LDS crossbar and no selects (lane exchanges by quad moves and two
+// ds_bpermute round trips before). Every lane of row 0, 1, 2, 3 returns the total of a, c,
+// b, d. Every addition has a fixed place, so the totals are the same bits on every run.
 // All 64 lanes must be active.
-template <int CTRL> __device__ __forceinline__ float dpp_mov(float x) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, false));
+__device__ __forceinline__ void fold_swap32(float x, float y, float &lo, float &hi) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    lo = __uint_as_float(r[0]);
+    hi = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void fold_swap16(float x, float y, float &even, float &odd) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    even = __uint_as_float(r[0]);
+    odd = __uint_as_float(r[1]);
 }
 __device__ __forceinline__ float wave_sum4(float a, float b, float c, float d) {
-    const uint32_t l = lane_id();
-    const bool o1 = (l & 1u) != 0, o2 = (l & 2u) != 0;
-    float k0 = o1 ? c : a;
-    float k1 = o1 ? d : b;
-    k0 += dpp_mov<0xb1>(o1 ? a : c);   // quad_perm [1,0,3,2]
-    k1 += dpp_mov<0xb1>(o1 ? b : d);
-    float k = o2 ? k1 : k0;
-    k += dpp_mov<0x4e>(o2 ? k0 : k1);  // quad_perm [2,3,0,1]
-    k = dpp_add<0x124, 0xf>(k);        // row_ror:4
-    k = dpp_add<0x128, 0xf>(k);        // row_ror:8
-    k += __shfl_xor(k, 16, 64);
-    k += __shfl_xor(k, 32, 64);
+    float l, h;
+    fold_swap32(a, b, l, h);
+    const float ab = l + h;
+    fold_swap32(c, d, l, h);
+    const float cd = l + h;
+    fold_swap16(ab, cd, l, h);
+    float k = l + h;
+    k = dpp_add<0x128, 0xf>(k);   // row_ror:8
+    k = dpp_add<0x124, 0xf>(k);   // row_ror:4
+    k = dpp_add<0x4e, 0xf>(k);    // quad_perm [2,3,0,1]
+    k = dpp_add<0xb1, 0xf>(k);    // quad_perm [1,0,3,2]
     return k;
 }
-// which of the four totals of wave_sum4 lane l (0..3) holds: 0 a, 1 b, 2 c, 3 d
-__device__ __forceinline__ uint32_t sum4_part(uint32_t l) { return ((l & 1u) << 1) | ((l >> 1) & 1u); }
+// one lane of each row writes: lane l (l % 16 == 0) holds total sum4_part(l) of wave_sum4
+// (0 a, 1 b, 2 c, 3 d)
+__device__ __forceinline__ bool sum4_writes(uint32_t l) { return (l & 15u) == 0; }
+__device__ __forceinline__ uint32_t sum4_part(uint32_t l) { return ((l >> 3) & 2u) | (l >> 5); }
 
 // inclusive prefix sum across the wave
 template <typename T> __device__ __forceinline__ T wave_incl_scan(T v) {
