@@ -23,6 +23,69 @@ namespace recogs {
 
 void launch_fill_u32(uint32_t *p, uint32_t v, int64_t count, hipStream_t st);
 
+// Before the tile form: zeroes the gradient slots (mult words of zero per key, the key count
+// on the device with dyn), and workgroup 0 writes the order in which the tiles are taken,
+// longest list first (classes of 8 entries; within a class any order, which changes no
+// result). Workgroups of several waves take a tile each and few are resident, so a long
+// list that starts late is a tail of its own: 195 -> 181 us for the blend at 1280x720 with
+// 32x16 tiles (1,800 workgroups, 768 resident). The order costs no launch: this fill is
+// needed anyway. (The forward's one-wave regions gain less than the launch an order of
+// their own would cost.)
+constexpr uint32_t kOrderBins = 1024;
+constexpr uint32_t kOrderPer = 16;                       // tiles per thread of the ordering workgroup
+constexpr uint32_t kOrderMax = 1024 * kOrderPer;         // more tiles than this: natural order
+__global__ __launch_bounds__(1024) void k_bwd_prep(uint4 *__restrict__ zero, const uint32_t *dyn, int64_t count,
+                                                   const uint2 *__restrict__ ranges, uint32_t ntiles,
+                                                   uint32_t *__restrict__ order) {
+    const uint32_t t = threadIdx.x;
+    if (order && blockIdx.x == 0) {
+        __shared__ uint32_t s_h[kOrderBins], s_w[16];
+        s_h[t] = 0;
+        uint32_t b[kOrderPer];
+#pragma unroll
+        for (uint32_t k = 0; k < kOrderPer; ++k) {
+            const uint32_t i = t + 1024u * k;
+            const uint2 r = i < ntiles ? ranges[i] : make_uint2(0u, 0u);
+            b[k] = kOrderBins - 1u - min((r.y - r.x) >> 3, kOrderBins - 1u);
+        }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t k = 0; k < kOrderPer; ++k)
+            if (t + 1024u * k < ntiles) atomicAdd(&s_h[b[k]], 1u);
+        __syncthreads();
+        const uint32_t mine = s_h[t], inc = wave_incl_scan(mine);
+        if (lane_id() == 63) s_w[t >> 6] = inc;
+        __syncthreads();
+        uint32_t pre = inc - mine;
+        for (uint32_t w = 0; w < (t >> 6); ++w) pre += s_w[w];
+        s_h[t] = pre;
+        __syncthreads();
+#pragma unroll
+        for (uint32_t k = 0; k < kOrderPer; ++k)
+            if (t + 1024u * k < ntiles) order[atomicAdd(&s_h[b[k]], 1u)] = t + 1024u * k;
+        return;
+    }
+    const uint32_t first = order ? 1u : 0u;
+    if (dyn) {
+        const int64_t c = (int64_t)*dyn;
+        count = c < count ? c : count;
+    }
+    for (int64_t i = (int64_t)(blockIdx.x - first) * 1024 + t; i < count; i += (int64_t)(gridDim.x - first) * 1024)
+        zero[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+// gk[0, count) zeroed (count slots, or *dyn of them if fewer); order (null: not written)
+// gets the ntiles tiles, longest list first. Returns whether order was written.
+bool launch_bwd_prep(float4 *gk, const uint32_t *dyn, int64_t count, const uint2 *ranges, uint32_t ntiles, uint32_t *order,
+                     hipStream_t st) {
+    if (ntiles > kOrderMax) order = nullptr;
+    int64_t blocks = (count + 4095) / 4096;
+    blocks = blocks < 1 ? 1 : (blocks > 2048 ? 2048 : blocks);
+    hipLaunchKernelGGL(k_bwd_prep, dim3((unsigned)(blocks + (order ? 1 : 0))), dim3(1024), 0, st, (uint4 *)gk, dyn, count,
+                       ranges, ntiles, order);
+    return order != nullptr;
+}
+
 // One splat replayed on one pixel: the forward's decisions with its arithmetic (act: the
 // entry is not past the pixel's last blended one; alpha at or above 1/255), the pixel's
 // state advanced, and the pixel's terms of the splat's sums: dr, dg, db and vs = sigma
@@ -55,7 +118,7 @@ __global__ __launch_bounds__(TW *TH / PPT) void k_blend_bwd(const uint2 *__restr
                                                            const uint32_t *__restrict__ koff, int W, int H, int tiles_x,
                                                            const float *__restrict__ image, const float *__restrict__ dldy,
                                                            const uint32_t *__restrict__ nproc,
-                                                           float4 *__restrict__ gk) {
+                                                           float4 *__restrict__ gk, const uint32_t *__restrict__ order) {
 #pragma clang fp contract(off)
     using Map = TileMap<TW, TH, PPT>;
     constexpr int NT = Map::NT;
@@ -68,7 +131,7 @@ __global__ __launch_bounds__(TW *TH / PPT) void k_blend_bwd(const uint2 *__restr
     __shared__ Stage sm;   // BlendRec.pad holds the (Gaussian, tile) slot, rgb.w the opacity
     __shared__ float4 s_acc[NW][BATCH];          // the waves' sums, where s_wrote has the record's bit
     __shared__ uint64_t s_wrote[NW][BATCH / 64];
-    const int tile = blockIdx.x;
+    const int tile = order ? (int)order[blockIdx.x] : (int)blockIdx.x;
     const uint32_t tcx = (uint32_t)(tile % tiles_x), tcy = (uint32_t)(tile / tiles_x);
     const int tx0 = (int)tcx * TW, ty0 = (int)tcy * TH;
     const int t = threadIdx.x;
@@ -170,26 +233,24 @@ __global__ __launch_bounds__(TW *TH / PPT) void k_blend_bwd(const uint2 *__restr
 #pragma unroll
         for (int c = 0; c < BATCH / 64; ++c) {
             uint64_t mm = todo[c], wrote = 0;
-            while (mm && !quit) {
-                const uint64_t bit = mm & (0ull - mm);
-                const int q = c * 64 + (int)__builtin_ctzll(mm);
-                mm &= mm - 1;
-                const uint32_t krel = start + q - rg.x;
-                if constexpr (L < 64) {
-                    if (!wave_ballot(krel < npmax)) {
-                        quit = true;
-                        break;
-                    }
-                }
+            // the records are read one ahead of their use: the LDS round trip of the next
+            // overlaps the arithmetic of the current one (two register sets, in turn): 204 ->
+            // 194 us per 720p view with 32x16 tiles; batches of 128 or 192 records with it, for
+            // one more workgroup per CU, took 205 and 198
+            struct Rec { float4 h, r1, r2; };
+            auto load = [&](int q) {
                 const float4 *br = reinterpret_cast<const float4 *>(&sm.r[q]);
-                const float4 h = br[0], r1 = br[1], r2 = br[2];
-                const ExpRow er = exp_row(r1, pxc - h.x);
+                return Rec{br[0], br[1], br[2]};
+            };
+            auto replay = [&](int q, const Rec &r) {
+                const uint32_t krel = start + q - rg.x;
+                const ExpRow er = exp_row(r.r1, pxc - r.h.x);
                 float ds, dr, dg, db;
                 bool any = false;
 #pragma unroll
                 for (int j = 0; j < PPT; ++j) {
                     float vs, vr, vg, vb;
-                    any |= bwd_step(P[j], er, r1, r2, pyc[j] - h.y, krel < np[j], vs, vr, vg, vb);
+                    any |= bwd_step(P[j], er, r.r1, r.r2, pyc[j] - r.h.y, krel < np[j], vs, vr, vg, vb);
                     if (j == 0) {   // (no adds of zero: x + 0 is not folded, for the sign of zero)
                         ds = vs; dr = vr; dg = vg; db = vb;
                     } else {
@@ -197,7 +258,7 @@ __global__ __launch_bounds__(TW *TH / PPT) void k_blend_bwd(const uint2 *__restr
                     }
                 }
                 if (wave_ballot(any)) {
-                    wrote |= bit;
+                    wrote |= 1ull << (q & 63);
                     if constexpr (L == 64) {
                         const float tot = wave_sum4(ds, dr, dg, db);
                         const uint32_t l = lane_id();
@@ -206,6 +267,33 @@ __global__ __launch_bounds__(TW *TH / PPT) void k_blend_bwd(const uint2 *__restr
                         ds = wave_sum_dpp<L>(ds); dr = wave_sum_dpp<L>(dr); dg = wave_sum_dpp<L>(dg); db = wave_sum_dpp<L>(db);
                         if (lane_id() == 0) s_acc[wv][q] = make_float4(ds, dr, dg, db);
                     }
+                }
+            };
+            auto done = [&](int q) {   // partial waves: every pixel has passed its last entry
+                if constexpr (L < 64) return !wave_ballot(start + (uint32_t)q - rg.x < npmax);
+                return false;
+            };
+            auto next = [&]() {   // the next record's position (any one when none is left)
+                const int q = c * 64 + (mm ? (int)__builtin_ctzll(mm) : 0);
+                mm &= mm - 1;
+                return q;
+            };
+            if (mm && !quit) {
+                int q0 = next(), q1 = 0;
+                Rec A = load(q0), B;
+                while (true) {
+                    const bool more1 = mm != 0;
+                    q1 = next();
+                    B = load(q1);
+                    if ((quit = done(q0))) break;
+                    replay(q0, A);
+                    if (!more1) break;
+                    const bool more0 = mm != 0;
+                    q0 = next();
+                    A = load(q0);
+                    if ((quit = done(q1))) break;
+                    replay(q1, B);
+                    if (!more0) break;
                 }
             }
             if (lane_id() == 0) s_wrote[wv][c] = wrote;
@@ -614,17 +702,18 @@ __global__ __launch_bounds__(1024) void k_loss_l2(const float *__restrict__ y, c
 template <int TW, int TH, int PPT>
 static void bwd_one(int ntiles, hipStream_t st, const uint2 *ranges, const uint32_t *vals, const SplatRec *rec,
                     const uint2 *rect, const uint32_t *koff, int W, int H, int tiles_x, const float *image,
-                    const float *dldy, const uint32_t *nproc, float4 *gk) {
+                    const float *dldy, const uint32_t *nproc, float4 *gk, const uint32_t *order) {
     hipLaunchKernelGGL((k_blend_bwd<TW, TH, PPT>), dim3(ntiles), dim3(TW * TH / PPT), 0, st, ranges, vals, rec, rect, koff, W,
-                       H, tiles_x, image, dldy, nproc, gk);
+                       H, tiles_x, image, dldy, nproc, gk, order);
 }
 
+// order: the tiles in the order they are taken (null: natural)
 bool launch_blend_bwd(int tw, int th, int ppt, int ntiles, const uint2 *ranges, const uint32_t *vals, const SplatRec *rec,
                       const uint2 *rect, const uint32_t *koff, int W, int H, int tiles_x, const float *image,
-                      const float *dldy, const uint32_t *nproc, float4 *gk, hipStream_t st) {
+                      const float *dldy, const uint32_t *nproc, float4 *gk, const uint32_t *order, hipStream_t st) {
 #define RECOGS_BWD_CASE(A, B, P)                                                                                 \
     if (tw == A && th == B && ppt == P) {                                                                        \
-        bwd_one<A, B, P>(ntiles, st, ranges, vals, rec, rect, koff, W, H, tiles_x, image, dldy, nproc, gk);      \
+        bwd_one<A, B, P>(ntiles, st, ranges, vals, rec, rect, koff, W, H, tiles_x, image, dldy, nproc, gk, order); \
         return true;                                                                                             \
     }
     RECOGS_BWD_CASE(16, 16, 1) RECOGS_BWD_CASE(16, 16, 2) RECOGS_BWD_CASE(16, 16, 4)

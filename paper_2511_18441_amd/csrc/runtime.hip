@@ -16,7 +16,6 @@ void launch_covariance(const float *, const float *, float *, int64_t, int64_t, 
 void launch_select(int, const SceneDev &, const CamDev &, const recogs_select_params &, uint8_t *, int32_t *, hipStream_t);
 void launch_recolor(int, const SceneDev &, int, void *, const uint8_t *, const float *, const float *, int, hipStream_t);
 void launch_fill_u32(uint32_t *, uint32_t, int64_t, hipStream_t);
-void launch_fill_u32_dyn(uint32_t *, uint32_t, const uint32_t *, uint32_t, int64_t, hipStream_t);
 void launch_preprocess(int, int, const SceneDev &, const CamDev &, const RecolorDev &, int, SplatRec *, float4 *,
                        uint32_t *, uint2 *, uint32_t *, hipStream_t, uint32_t *, int64_t);
 void launch_scan(const uint32_t *, const uint32_t *, uint32_t *, int64_t, uint64_t *, uint32_t *, uint32_t *, uint32_t *,
@@ -43,7 +42,8 @@ int radix_sort_tile_depth64(uint64_t *, uint32_t *, uint64_t *, uint32_t *, uint
 int radix_sort_u32(uint32_t *, uint32_t *, uint32_t *, uint32_t *, uint32_t, uint32_t, int, uint32_t *, uint32_t *,
                    hipStream_t, const EmitFold * = nullptr, bool = false);
 bool launch_blend_bwd(int, int, int, int, const uint2 *, const uint32_t *, const SplatRec *, const uint2 *, const uint32_t *,
-                      int, int, int, const float *, const float *, const uint32_t *, float4 *, hipStream_t);
+                      int, int, int, const float *, const float *, const uint32_t *, float4 *, const uint32_t *, hipStream_t);
+bool launch_bwd_prep(float4 *, const uint32_t *, int64_t, const uint2 *, uint32_t, uint32_t *, hipStream_t);
 void launch_grad_finish(const float4 *, const uint32_t *, const float4 *, const uint32_t *, int64_t, const float *, float *,
                         float *, float *, float *, int, const float *, int64_t, const CamDev &, int, hipStream_t, float *,
                         float *, float *, const AdamArgs *, uint64_t, const uint32_t *);
@@ -755,17 +755,18 @@ static recogs_status backward_impl(const recogs_scene *scene, const recogs_camer
                                          at<uint2>(ws, ws->off_rect), koff, cam->width, cam->height, ws->tiles_x, image,
                                          dL_dimage, at<uint32_t>(ws, ws->off_nproc), sub, fw, (uint32_t)cap,
                                          (uint32_t)bwd_flag_stride(ws), gk, stream);
-        } else if (dyn_keys) {
-            launch_fill_u32_dyn((uint32_t *)gk, 0u, at<uint32_t>(ws, ws->off_header) + H_KEFF, 4u,
-                                4 * ws->key_capacity, stream);
-            ok = launch_blend_bwd(opts->tile_w, opts->tile_h, opts->px_per_thread, ntiles, at<uint2>(ws, ws->off_ranges),
-                                  vals, at<SplatRec>(ws, ws->off_rec), at<uint2>(ws, ws->off_rect), koff, cam->width,
-                                  cam->height, ws->tiles_x, image, dL_dimage, at<uint32_t>(ws, ws->off_nproc), gk, stream);
         } else {
-            launch_fill_u32((uint32_t *)gk, 0u, 4 * ws->num_keys, stream);
-            ok = launch_blend_bwd(opts->tile_w, opts->tile_h, opts->px_per_thread, ntiles, at<uint2>(ws, ws->off_ranges),
-                                  vals, at<SplatRec>(ws, ws->off_rec), at<uint2>(ws, ws->off_rect), koff, cam->width,
-                                  cam->height, ws->tiles_x, image, dL_dimage, at<uint32_t>(ws, ws->off_nproc), gk, stream);
+            // the value buffer that the key sort left free holds the tiles' order, where it
+            // is long enough
+            uint32_t *order = at<uint32_t>(ws, ws->sorted_in_alt ? ws->off_vals0 : ws->off_vals1);
+            if (ws->key_capacity < ntiles) order = nullptr;
+            const uint2 *ranges = at<uint2>(ws, ws->off_ranges);
+            if (!launch_bwd_prep(gk, dyn_keys ? at<uint32_t>(ws, ws->off_header) + H_KEFF : nullptr,
+                                 dyn_keys ? ws->key_capacity : ws->num_keys, ranges, (uint32_t)ntiles, order, stream))
+                order = nullptr;
+            ok = launch_blend_bwd(opts->tile_w, opts->tile_h, opts->px_per_thread, ntiles, ranges, vals,
+                                  at<SplatRec>(ws, ws->off_rec), at<uint2>(ws, ws->off_rect), koff, cam->width, cam->height,
+                                  ws->tiles_x, image, dL_dimage, at<uint32_t>(ws, ws->off_nproc), gk, order, stream);
         }
         if (!ok) return fail(RECOGS_ERR_UNSUPPORTED, "no backward kernel for this tile / px_per_thread");
     }
