@@ -10,18 +10,20 @@
 //      128), so far-away stray points do not coarsen the grid for the rest;
 //   2. each point's cell (floor((x - min) / h) per axis) goes to the slot made of its
 //      coordinates modulo powers of two (2^b slots, b = log2 of about 2n, at least 4 bits
-//      per axis); a radix sort by slot and a range pass give each slot its run of points
-//      (slot order is also the query order: queries of one wave start in nearby cells);
-//   3. per query, the cells of Chebyshev rings r = 0, 1, ... are scanned (no two cells of
-//      one search share a slot; points of far cells that do are scanned too), keeping the k
-//      smallest squared distances in registers (sorted insertion): rings 0-1 one thread
-//      per query, further rings one wave per query (the lanes split a ring's cells, so a
-//      few sparse neighbourhoods do not hold whole waves back); after ring r >= 1 the
-//      search stops once the k-th distance is within (r - 1/16) h, the distance below
-//      which no unscanned cell lies (the 1/16 absorbs float32 rounding of the cell
-//      coordinates). A query whose rings reach kOlMaxRing without that bound (a far
-//      stray point) is deferred to a second kernel that scans the whole cloud with one
-//      workgroup per query (strided per-thread lists merged in LDS).
+//      per axis); a radix sort by slot orders the points, and a binary search gives each
+//      slot's first point, so the points of consecutive slots are one run (slot order is
+//      also the query order: queries of one wave start in nearby cells);
+//   3. per query, the cubes of cells of Chebyshev radius 1, then 2, then 5 are searched (no
+//      two cells of one cube share a slot; points of far cells that do are scanned too),
+//      a row of cells along x being one run of points; the search ends once the k-th
+//      distance is within (r - 1/16) h, the distance below which no unscanned cell lies
+//      (the 1/16 absorbs float32 rounding of the cell coordinates). A query has 2, 16 and
+//      64 lanes in the three searches, which merge their lists of the k smallest. Queries
+//      that even the largest cube leaves open (far stray points) go to a search of the
+//      whole cloud by the bounding boxes of its runs of 64 points.
+//      314k points (a brush selection): 285 us for the four, against 980 with one thread
+//      per query over the 27 cells one by one, one wave per query with a cell per lane for
+//      the rest, and a scan of the whole cloud for each stray point.
 //   4. mu and sigma from compensated float32 sums (float-float, TwoSum) in a fixed order:
 //      a pass for the sum of D, a pass for the sum of (D - mu)^2; the threshold, the keep
 //      mask (float32 comparison) and the compaction of the kept points (input order)
@@ -32,19 +34,20 @@ namespace recogs {
 
 int radix_sort_u32(uint32_t *, uint32_t *, uint32_t *, uint32_t *, uint32_t, uint32_t, int, uint32_t *, uint32_t *,
                    hipStream_t, const EmitFold * = nullptr, bool = false);
-void launch_ranges32(const uint32_t *, uint32_t, uint2 *, hipStream_t, const uint32_t *);
-void launch_fill_u32(uint32_t *, uint32_t, int64_t, hipStream_t);
 void launch_excl_scan_u32(uint32_t *, uint32_t, uint32_t *, hipStream_t);
 
 constexpr int kOlBins = 1024;
 constexpr int kOlMaxDim = 128;
-constexpr int kOlThreadRing = 2;               // rings searched by the one-thread-per-query pass
-constexpr int kOlMaxRing = 6;                  // rings searched by the wave-per-query pass
-constexpr int kOlWaveBlocks = 2048;            // grid of the wave-per-query pass (4 waves each)
-static_assert(2 * (kOlMaxRing - 1) + 1 <= 16, "one search's cells must fit in 16 slot residues per axis");
-constexpr int kOlFarBlocks = 1024;             // grid of the whole-cloud scans (grid-stride over the queries)
-constexpr int kOlFarThreads = 512;             // threads per whole-cloud scan (LDS: 512 k floats, 64 KB at k = 32)
+constexpr int kOlRing1 = 1, kOlRing2 = 2, kOlRing3 = 5;   // cube radii of the three searches
+constexpr int kOlR1 = 1, kOlC1 = 2, kOlR2 = 4, kOlC2 = 4, kOlR3 = 16, kOlC3 = 4;   // their lanes per query: rows x candidates
+constexpr int kOlListBlocks = 2048;            // grid of the second and third (grid-stride over their lists)
+static_assert(2 * kOlRing3 + 1 <= 16, "one search's cells must fit in 16 slot residues per axis");
+constexpr int kOlLeaf = 64;                    // points per bounding box of the whole-cloud search
+constexpr int kOlFarBlocks = 1024;             // grid of the whole-cloud searches (grid-stride over the queries)
+constexpr int kOlFarThreads = 512;
 constexpr int kOlRedBlocks = 512;              // grid of the reductions (grid-stride)
+constexpr int64_t kOlSample = 32768;           // points of the histograms' sample, about
+constexpr uint32_t kOlScanFold = 2048;         // most workgroup counts that the compaction sums by itself
 constexpr int kOlItems = 4;                    // points per thread of the keep/compaction passes
 constexpr int kOlBlock = 256 * kOlItems;
 constexpr float kOlClamp = 1048576.f;          // cell coordinates are clamped to +-2^20
@@ -60,8 +63,8 @@ struct OlHdr {
     float mn[3], mx[3];   // bounding box
     float h, inv_h;       // cell size and its reciprocal
     uint32_t bx, by, bz;  // slot bits per axis
-    uint32_t ndefer;      // queries left to the whole-cloud scan
-    uint32_t nslow;       // queries left to the wave-per-query search
+    uint32_t ndefer;      // queries left to the whole-cloud search
+    uint32_t nslow[2];    // queries left to the second and to the third cube search
     float thr;            // mu + std_ratio sigma
     float mu, sigma;
 };
@@ -97,10 +100,11 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
-// 1a. per-workgroup bounding boxes -> part[blk][6]
+// 1a. per-workgroup bounding boxes -> part[blk][6]; also zeroes the histograms
 __global__ __launch_bounds__(256) void k_ol_bbox(const float *__restrict__ pts, int64_t n, int64_t stride,
-                                                 float *__restrict__ part) {
+                                                 float *__restrict__ part, uint32_t *__restrict__ hist) {
     __shared__ float s[4][6];
+    for (int k = (int)(blockIdx.x * 256 + threadIdx.x); k < 3 * kOlBins; k += (int)gridDim.x * 256) hist[k] = 0u;
     float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
         float p[3];
@@ -131,38 +135,41 @@ __global__ __launch_bounds__(256) void k_ol_bbox(const float *__restrict__ pts, 
     }
 }
 
-// 1b. final box: wave w (of 6) reduces bound w over the partials
-__global__ __launch_bounds__(384) void k_ol_bbox_final(const float *__restrict__ part, int nblk, OlHdr *__restrict__ hdr) {
-    const int a = threadIdx.x >> 6, l = (int)lane_id();
-    const bool lo = a < 3;
-    float v = lo ? INFINITY : -INFINITY;
-    for (int b = l; b < nblk; b += 64) v = lo ? fminf(v, part[b * 6 + a]) : fmaxf(v, part[b * 6 + a]);
-    v = lo ? wave_min(v) : wave_max(v);
-    if (l == 0) {
-        if (lo) hdr->mn[a] = v;
-        else hdr->mx[a - 3] = v;
-        if (a == 0) {
-            hdr->ndefer = 0;
-            hdr->nslow = 0;
+// 1b. per-axis histograms over the box (LDS counts, then one atomic per bin and
+// workgroup; integer counts, so the result is independent of the order), of every step-th
+// point: they only place the cell size, which no result depends on, and neighbouring
+// points fall into the same bins, whose LDS atomics then wait for each other (15 us over
+// all points of a 314k cloud). Every workgroup reduces the partial boxes for itself (wave w the bounds w and w + 4); workgroup 0 stores
+// the box and clears the queues' counts.
+__global__ __launch_bounds__(256) void k_ol_hist(const float *__restrict__ pts, int64_t n, int64_t stride,
+                                                 int64_t step, const float *__restrict__ part, int nblk,
+                                                 OlHdr *__restrict__ hdr, uint32_t *__restrict__ hist) {
+    __shared__ uint32_t s_h[3 * kOlBins];
+    __shared__ float s_box[6];
+    for (int k = threadIdx.x; k < 3 * kOlBins; k += 256) s_h[k] = 0;
+    for (int a = (int)(threadIdx.x >> 6); a < 6; a += 4) {
+        const bool lo = a < 3;
+        float v = lo ? INFINITY : -INFINITY;
+        for (int b = (int)lane_id(); b < nblk; b += 64) v = lo ? fminf(v, part[b * 6 + a]) : fmaxf(v, part[b * 6 + a]);
+        v = lo ? wave_min(v) : wave_max(v);
+        if (lane_id() == 0) {
+            s_box[a] = v;
+            if (blockIdx.x == 0) {
+                if (lo) hdr->mn[a] = v;
+                else hdr->mx[a - 3] = v;
+            }
         }
     }
-}
-
-// 1c. per-axis histograms over the box (LDS counts, then one atomic per bin and
-// workgroup; integer counts, so the result is independent of the order)
-__global__ __launch_bounds__(256) void k_ol_hist(const float *__restrict__ pts, int64_t n, int64_t stride,
-                                                 const OlHdr *__restrict__ hdr, uint32_t *__restrict__ hist) {
-    __shared__ uint32_t s_h[3 * kOlBins];
-    for (int k = threadIdx.x; k < 3 * kOlBins; k += 256) s_h[k] = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) hdr->ndefer = hdr->nslow[0] = hdr->nslow[1] = 0;
     __syncthreads();
     float mn[3], sc[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        mn[a] = hdr->mn[a];
-        const float e = hdr->mx[a] - mn[a];
+        mn[a] = s_box[a];
+        const float e = s_box[3 + a] - mn[a];
         sc[a] = e > 0.f ? (float)kOlBins / e : 0.f;
     }
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    for (int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * step; i < n; i += (int64_t)gridDim.x * 256 * step) {
         float p[3];
         ol_load(pts, stride, i, p[0], p[1], p[2]);
 #pragma unroll
@@ -177,15 +184,16 @@ __global__ __launch_bounds__(256) void k_ol_hist(const float *__restrict__ pts, 
         if (s_h[k]) atomicAdd(&hist[k], s_h[k]);
 }
 
-// 1d. cell size from the 1%-99% quantile extents: wave a scans axis a's 1024 bins (16
+// 1c. cell size from the 1%-99% quantile extents: wave a scans axis a's 1024 bins (16
 // per lane, then a wave scan) and finds the first bins whose cumulative count passes 1%
 // and 99% of the points; then thread 0 sets h.
-__global__ __launch_bounds__(192) void k_ol_setup(const uint32_t *__restrict__ hist, int64_t n, uint32_t slot_bits,
+// (ns: the histograms' points)
+__global__ __launch_bounds__(192) void k_ol_setup(const uint32_t *__restrict__ hist, int64_t ns, int64_t n, uint32_t slot_bits,
                                                   OlHdr *__restrict__ hdr) {
     __shared__ float s_ext[3];
     constexpr int PER = kOlBins / 64;
     const int a = threadIdx.x >> 6, l = (int)lane_id();
-    const uint64_t lo_need = (uint64_t)n / 100u, hi_need = (uint64_t)n * 99u / 100u;
+    const uint64_t lo_need = (uint64_t)ns / 100u, hi_need = (uint64_t)ns * 99u / 100u;
     uint32_t c[PER];
     uint32_t mine = 0;
 #pragma unroll
@@ -208,7 +216,7 @@ __global__ __launch_bounds__(192) void k_ol_setup(const uint32_t *__restrict__ h
         return best;
     };
     int blo = first_over(lo_need);
-    int bhi = first_over(hi_need < (uint64_t)n ? hi_need : (uint64_t)n - 1);
+    int bhi = first_over(hi_need < (uint64_t)ns ? hi_need : (uint64_t)ns - 1);
     blo = blo >= kOlBins ? 0 : blo;
     bhi = bhi >= kOlBins ? kOlBins - 1 : bhi;
     if (l == 0) {
@@ -245,237 +253,284 @@ __global__ __launch_bounds__(256) void k_ol_key(const float *__restrict__ pts, i
     vals[i] = (uint32_t)i;
 }
 
-// 2b. the points in slot order as float4 (x, y, z, input index bits): one 16-byte load
-// per candidate in the searches below
+// number of keys below `key` among the sorted keys[0, n), by the whole wave: 64 probes a
+// round, so n is cut by 65 per memory round trip
+__device__ __forceinline__ uint32_t wave_lower_bound(const uint32_t *__restrict__ keys, uint32_t n, uint32_t key) {
+    uint32_t lo = 0, len = n;
+    while (len > 0) {
+        const uint32_t step = (len + 64u) / 65u, p = step * (lane_id() + 1u) - 1u;   // probe within [0, len)
+        const bool below = p < len && keys[lo + p] < key;
+        const uint32_t c = (uint32_t)__builtin_popcountll(wave_ballot(below));
+        lo += c * step;
+        const uint32_t rest = len - c * step;   // up to the probe that was not below, if any
+        len = c < 64u ? min(step - 1u, rest) : rest;
+    }
+    return lo;
+}
+
+// 2b. workgroups [0, sblk): each slot's first point in slot order, start[s] = the number of
+// keys below s, for the slots and one past the last (a run of slots [s, t) holds the points
+// [start[s], start[t])): a wave finds where its 64 slots begin and end (14 us with a
+// binary search over all keys per slot, now 6 with the gather), each lane its own slot
+// between them.
+// The others: the points in slot order as float4 (x, y, z, input index bits): one 16-byte
+// load per candidate in the searches below; and the bounding box of each run of kOlLeaf
+// (one wave's) as two float4.
 __global__ __launch_bounds__(256) void k_ol_gather(const float *__restrict__ pts, int64_t n, int64_t stride,
-                                                   const uint32_t *__restrict__ svals, float4 *__restrict__ spts) {
-    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (j >= n) return;
-    const uint32_t i = svals[j];
-    float x, y, z;
-    ol_load(pts, stride, i, x, y, z);
-    spts[j] = make_float4(x, y, z, __uint_as_float(i));
+                                                   const uint32_t *__restrict__ keys, const uint32_t *__restrict__ svals,
+                                                   uint32_t slots, uint32_t sblk, uint32_t *__restrict__ start,
+                                                   float4 *__restrict__ spts, float4 *__restrict__ boxes) {
+    if (blockIdx.x < sblk) {
+        const uint32_t s0 = blockIdx.x * 256u + (threadIdx.x & ~63u), s = s0 + lane_id();
+        if (s0 > slots) return;
+        uint32_t lo = wave_lower_bound(keys, (uint32_t)n, s0);
+        uint32_t hi = lo + wave_lower_bound(keys + lo, (uint32_t)n - lo, s0 + 64u);
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (keys[mid] < s) lo = mid + 1;
+            else hi = mid;
+        }
+        if (s <= slots) start[s] = lo;
+        return;
+    }
+    static_assert(kOlLeaf == 64, "a leaf is a wave's points");
+    const int64_t j = (int64_t)(blockIdx.x - sblk) * 256 + threadIdx.x;
+    float p[3] = {0.f, 0.f, 0.f};
+    if (j < n) {
+        const uint32_t i = svals[j];
+        ol_load(pts, stride, i, p[0], p[1], p[2]);
+        spts[j] = make_float4(p[0], p[1], p[2], __uint_as_float(i));
+    }
+    float lo[3], hi[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        lo[a] = wave_min(j < n ? p[a] : INFINITY);
+        hi[a] = wave_max(j < n ? p[a] : -INFINITY);
+    }
+    if (lane_id() == 0 && j < n) {
+        boxes[2 * (j / kOlLeaf)] = make_float4(lo[0], lo[1], lo[2], 0.f);
+        boxes[2 * (j / kOlLeaf) + 1] = make_float4(hi[0], hi[1], hi[2], 0.f);
+    }
 }
 
-template <int K>
-__device__ __forceinline__ void ol_insert(float (&best)[K], float d2) {
-    if (!(d2 < best[K - 1])) return;
+// The K smallest squared distances, ascending (+inf: none yet). One more is put in its
+// place by one median of three per entry: entry q becomes the median of d2 and the old
+// entries q - 1 and q.
+template <int K> __device__ __forceinline__ void ol_insert(float (&best)[K], float d2) {
+    if (d2 < best[K - 1]) {
 #pragma unroll
-    for (int q = K - 1; q > 0; --q) best[q] = d2 < best[q - 1] ? best[q - 1] : (d2 < best[q] ? d2 : best[q]);
-    best[0] = d2 < best[0] ? d2 : best[0];
+        for (int q = K - 1; q > 0; --q) best[q] = __builtin_amdgcn_fmed3f(d2, best[q - 1], best[q]);
+        best[0] = fminf(best[0], d2);
+    }
 }
-
-// One slot's candidates [rg.x, rg.y) of the slot-ordered points against query i at
-// (x, y, z); four loads in flight.
-template <int K>
-__device__ __forceinline__ void ol_scan_cell(const float4 *__restrict__ spts, uint2 rg, uint32_t i, float x, float y,
-                                             float z, float (&best)[K]) {
-    for (uint32_t j = rg.x; j < rg.y; j += 4) {
-        float4 c[4];
+__device__ __forceinline__ void ol_ce(float &a, float &b) {   // compare and exchange (as bits: no value is negative or NaN)
+    const uint32_t u = __float_as_uint(a), v = __float_as_uint(b);
+    a = __uint_as_float(min(u, v));
+    b = __uint_as_float(max(u, v));
+}
+// every lane of an aligned group of G lanes <- the K smallest of the group's lists: the
+// element-wise minima of a list and its partner's reversed hold the K smallest of both as
+// a bitonic sequence, which log2 K rounds of exchanges sort
+template <int K, int G> __device__ __forceinline__ void ol_merge_lanes(float (&best)[K]) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) c[u] = j + u < rg.y ? spts[j + u] : make_float4(0.f, 0.f, 0.f, __uint_as_float(i));
+    for (int o = 1; o < G; o <<= 1) {
+        float t[K];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (__float_as_uint(c[u].w) == i) continue;   // the query itself, or past the range
+        for (int a = 0; a < K; ++a) t[a] = __shfl_xor(best[a], o, 64);
+#pragma unroll
+        for (int a = 0; a < K; ++a) best[K - 1 - a] = fminf(best[K - 1 - a], t[a]);
+#pragma unroll
+        for (int s = K / 2; s > 0; s >>= 1)
+#pragma unroll
+            for (int a = 0; a < K; ++a)
+                if (!(a & s)) ol_ce(best[a], best[a + s]);
+    }
+}
+// N candidates, loaded together, against query i at (x, y, z); the first `count` count
+template <int K, int N>
+__device__ __forceinline__ void ol_take(float (&best)[K], const float4 (&c)[N], uint32_t count, uint32_t i, float x, float y,
+                                        float z) {
+#pragma unroll
+    for (uint32_t u = 0; u < (uint32_t)N; ++u) {
+        if (u < count) {   // (skipped by the wave once none of its lanes has more)
             const float ex = c[u].x - x, ey = c[u].y - y, ez = c[u].z - z;
-            ol_insert<K>(best, __builtin_fmaf(ex, ex, __builtin_fmaf(ey, ey, ez * ez)));
+            const float d2 = __builtin_fmaf(ex, ex, __builtin_fmaf(ey, ey, ez * ez));
+            if (__float_as_uint(c[u].w) != i) ol_insert<K>(best, d2);   // (i: the query itself)
         }
     }
 }
-
-// 3. k nearest neighbours of every point (one thread per point, slot order), rings 0
-// and 1 only: a query not settled by then goes to the wave-per-query search (slow list,
-// slot positions), a query beyond the coordinate guard to the whole-cloud scan.
-template <int K>
-__global__ __launch_bounds__(256) void k_ol_knn(const float4 *__restrict__ spts, int64_t n, OlHdr *hdr,
-                                                const uint2 *__restrict__ ranges, uint32_t *__restrict__ slow,
-                                                uint32_t *__restrict__ defer, float *__restrict__ dmean) {
-    const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (s >= n) return;
-    const float4 me = spts[s];
-    const uint32_t i = __float_as_uint(me.w);
-    const float x = me.x, y = me.y, z = me.z;
-    const float mnx = hdr->mn[0], mny = hdr->mn[1], mnz = hdr->mn[2], ih = hdr->inv_h, h = hdr->h;
-    const uint32_t bx = hdr->bx, by = hdr->by, bz = hdr->bz;
-    const int cx = ol_coord(x, mnx, ih), cy = ol_coord(y, mny, ih), cz = ol_coord(z, mnz, ih);
-    const int want = n - 1 < (int64_t)K ? (int)(n - 1) : K;
-    float best[K];
-#pragma unroll
-    for (int q = 0; q < K; ++q) best[q] = INFINITY;
-    bool done = want == 0;
-    const bool clamped = fabsf((x - mnx) * ih) > kOlQueryLimit || fabsf((y - mny) * ih) > kOlQueryLimit ||
-                         fabsf((z - mnz) * ih) > kOlQueryLimit;
-    static_assert(kOlThreadRing == 2, "the one-thread pass covers the 3 x 3 x 3 cells of rings 0 and 1");
-    if (!done && !clamped) {
-        // the 27 slot ranges first (independent loads), then the cells' candidates
-        uint2 rg[27];
-#pragma unroll
-        for (int t = 0; t < 27; ++t)
-            rg[t] = ranges[ol_slot(cx + t % 3 - 1, cy + (t / 3) % 3 - 1, cz + t / 9 - 1, bx, by, bz)];
-#pragma unroll 1
-        for (int t = 0; t < 27; ++t) ol_scan_cell<K>(spts, rg[t], i, x, y, z, best);
-        float kth = best[0];
-#pragma unroll
-        for (int q = 1; q < K; ++q) kth = q == want - 1 ? best[q] : kth;
-        const float bound = (1.f - kOlMargin) * h;
-        done = kth <= bound * bound;
-    }
-    if (!done) {
-        if (clamped) defer[atomicAdd(&hdr->ndefer, 1u)] = i;
-        else slow[atomicAdd(&hdr->nslow, 1u)] = (uint32_t)s;
-        return;
-    }
+template <int K> __device__ __forceinline__ float ol_mean(const float (&best)[K], int want) {
     float sum = 0.f;
 #pragma unroll
     for (int q = 0; q < K; ++q) sum += q < want ? sqrtf(best[q]) : 0.f;
-    dmean[i] = want > 0 ? sum / (float)want : 0.f;
+    return want > 0 ? sum / (float)want : 0.f;
 }
 
-// 3b. the slow queries, one wave each (grid-stride over the list): the lanes split
-// each ring's cells (cube index t -> offsets, ring cells only) and keep their own k
-// smallest squared distances. The stop test after ring r counts, over the lanes, the
-// entries of their lists within the bound: the k-th smallest of the union is within it
-// iff at least k are (each of the k smallest overall is in its lane's k smallest). The
-// 64 lists are then merged pairwise in LDS (6 rounds, wave-level ordering only).
-// Queries not settled by ring kOlMaxRing - 1 go to the whole-cloud scan.
-template <int K>
-__global__ __launch_bounds__(256) void k_ol_knn_wave(const float4 *__restrict__ spts, int64_t n, OlHdr *hdr,
-                                                     const uint2 *__restrict__ ranges, const uint32_t *__restrict__ slow,
-                                                     uint32_t *__restrict__ defer, float *__restrict__ dmean) {
-    __shared__ float s_l[4][64 * K];
-    const int wv = (int)(threadIdx.x >> 6), l = (int)lane_id();
-    float *Ls = s_l[wv];
-    const uint32_t ns = hdr->nslow;
-    const uint32_t waves = gridDim.x * 4u;
+// 3. k nearest neighbours within the cube of cells of radius RING, G = GR GC consecutive
+// lanes per query: its (2 RING + 1)^2 rows of cells are dealt to GR groups, and GC lanes
+// take neighbouring candidates of a row (one line of memory then serves several lanes).
+// More lanes per query fill the GPU and balance the rows, fewer leave less to merge:
+// measured at 314k points, (GR, GC) of the radius-1 search (1, 1) 135, (1, 2) 119, (1, 4) 137,
+// (1, 8) 193 us; of the radius-2 search (4, 2) 91, (8, 2) 76, (4, 4) 68; of the radius-5
+// search (16, 2) 75, (8, 8) 49, (16, 4) 42. The queries are all points in slot order (list null) or the listed slot positions, *nlist of
+// them, grid-stride. A query not settled goes to the list `slow` (or, with slow null, to
+// the whole-cloud search, as does any beyond the coordinate guard).
+template <int K, int RING, int GR, int GC>
+__global__ __launch_bounds__(256) void k_ol_knn(const float4 *__restrict__ spts, int64_t n, OlHdr *hdr,
+                                                const uint32_t *__restrict__ start, const uint32_t *__restrict__ list,
+                                                const uint32_t *nlist, uint32_t *__restrict__ slow, uint32_t *nslow,
+                                                uint32_t *__restrict__ defer, float *__restrict__ dmean) {
+    constexpr int SIDE = 2 * RING + 1, ROWS = SIDE * SIDE, G = GR * GC;
     const float mnx = hdr->mn[0], mny = hdr->mn[1], mnz = hdr->mn[2], ih = hdr->inv_h, h = hdr->h;
     const uint32_t bx = hdr->bx, by = hdr->by, bz = hdr->bz;
+    const uint32_t mx = (1u << bx) - 1u, my = (1u << by) - 1u, mz = (1u << bz) - 1u;
     const int want = n - 1 < (int64_t)K ? (int)(n - 1) : K;
-    for (uint32_t q = blockIdx.x * 4u + (uint32_t)wv; q < ns; q += waves) {
-        const float4 me = spts[slow[q]];
+    const uint32_t total = list ? *nlist : (uint32_t)n;
+    const int g = (int)(threadIdx.x % G), gr = g / GC;
+    const uint32_t gc = (uint32_t)(g % GC);
+    const uint32_t last = (uint32_t)n - 1u;
+    for (uint32_t q = (blockIdx.x * 256u + threadIdx.x) / G; q < total; q += gridDim.x * (256u / G)) {
+        const uint32_t s = list ? list[q] : q;
+        const float4 me = spts[s];
         const uint32_t i = __float_as_uint(me.w);
         const float x = me.x, y = me.y, z = me.z;
-        const int cx = ol_coord(x, mnx, ih), cy = ol_coord(y, mny, ih), cz = ol_coord(z, mnz, ih);
         float best[K];
 #pragma unroll
         for (int a = 0; a < K; ++a) best[a] = INFINITY;
-        bool done = false;
-        for (int r = 0; r < kOlMaxRing && !done; ++r) {
-            const int side = 2 * r + 1, cube = side * side * side;
-            for (int t = l; t < cube; t += 64) {
-                const int dx = t % side - r, dy = (t / side) % side - r, dz = t / (side * side) - r;
-                if (max(abs(dx), max(abs(dy), abs(dz))) != r) continue;   // inner cells: earlier rings
-                const int qx = cx + dx, qy = cy + dy, qz = cz + dz;
-                ol_scan_cell<K>(spts, ranges[ol_slot(qx, qy, qz, bx, by, bz)], i, x, y, z, best);
-            }
-            if (r >= 1) {
-                const float bound = ((float)r - kOlMargin) * h, b2 = bound * bound;
-                int c = 0;
+        const bool clamped = fabsf((x - mnx) * ih) > kOlQueryLimit || fabsf((y - mny) * ih) > kOlQueryLimit ||
+                             fabsf((z - mnz) * ih) > kOlQueryLimit;
+        bool done = want == 0;
+        if (!done && !clamped) {
+            const uint32_t cx = (uint32_t)ol_coord(x, mnx, ih), cy = (uint32_t)ol_coord(y, mny, ih),
+                           cz = (uint32_t)ol_coord(z, mnz, ih);
+            // a row of cells is one run of slots, or two where it wraps around the residues
+            const uint32_t x0 = (cx - RING) & mx, x1 = (cx + RING) & mx;
+            const bool wrap = x0 > x1;
+            auto row = [&](int r) {   // the row's first slot (x residue 0)
+                return (((cy + (uint32_t)(r % SIDE) - RING) & my) << bx) | (((cz + (uint32_t)(r / SIDE) - RING) & mz) << (bx + by));
+            };
+            constexpr uint32_t NB = 8;   // candidates in flight per lane
+            auto run = [&](uint32_t a, uint32_t b) {
+                for (uint32_t j = a + gc; j < b; j += NB * GC) {
+                    float4 c[NB];
+                    const uint32_t left = (b - j + GC - 1) / GC;   // this lane's candidates
 #pragma unroll
-                for (int a = 0; a < K; ++a) c += best[a] <= b2 ? 1 : 0;
-                for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
-                done = c >= want;
-            }
-        }
-        if (!done) {
-            if (l == 0) defer[atomicAdd(&hdr->ndefer, 1u)] = i;
-            continue;
-        }
-#pragma unroll
-        for (int a = 0; a < K; ++a) Ls[l * K + a] = best[a];
-        wave_sync();
-        for (int sp = 1; sp < 64; sp <<= 1) {
-            if ((l & (2 * sp - 1)) == 0) {
-                const float *A = Ls + l * K, *B = Ls + (l + sp) * K;
-                float m[K];
-                int ia = 0, ib = 0;
-#pragma unroll
-                for (int a = 0; a < K; ++a) {
-                    const float va = A[ia], vb = B[ib];
-                    const bool ta = va <= vb;
-                    m[a] = ta ? va : vb;
-                    ia += ta ? 1 : 0;
-                    ib += ta ? 0 : 1;
+                    for (uint32_t u = 0; u < NB; ++u) c[u] = spts[min(j + u * GC, last)];
+                    ol_take<K, NB>(best, c, left, i, x, y, z);
                 }
-#pragma unroll
-                for (int a = 0; a < K; ++a) Ls[l * K + a] = m[a];
+            };
+            uint32_t base = row(gr < ROWS ? gr : 0);
+            uint32_t a = start[base + x0], b = start[base + (wrap ? mx : x1) + 1u];
+            for (int r = gr; r < ROWS; r += GR) {
+                // the next row's run is looked up while this one is scanned
+                const int rn = r + GR;
+                const uint32_t nbase = row(rn < ROWS ? rn : r);
+                const uint32_t na = start[nbase + x0], nb = start[nbase + (wrap ? mx : x1) + 1u];
+                run(a, b);
+                if (wrap) run(start[base], start[base + x1 + 1u]);
+                base = nbase;
+                a = na;
+                b = nb;
             }
-            wave_sync();
+            ol_merge_lanes<K, G>(best);
+            float kth = best[0];
+#pragma unroll
+            for (int a2 = 1; a2 < K; ++a2) kth = a2 == want - 1 ? best[a2] : kth;
+            const float bound = ((float)RING - kOlMargin) * h;
+            done = kth <= bound * bound;
         }
-        if (l == 0) {
-            float sum = 0.f;
-            for (int a = 0; a < want; ++a) sum += sqrtf(Ls[a]);
-            dmean[i] = want > 0 ? sum / (float)want : 0.f;
+        if (g == 0) {
+            if (done) dmean[i] = ol_mean<K>(best, want);
+            else if (clamped || !slow) defer[atomicAdd(&hdr->ndefer, 1u)] = i;
+            else slow[atomicAdd(nslow, 1u)] = s;
         }
-        wave_sync();   // the lists are rewritten by the next query
     }
 }
 
-// 3c. the deferred queries, one workgroup each (grid-stride over the list): every
-// thread keeps the k smallest squared distances of a strided share of the cloud, then
-// the kOlFarThreads sorted lists are merged pairwise in LDS (9 rounds).
+// 3b. the deferred queries, one workgroup each (grid-stride over the list): each thread
+// tests the boxes of the cloud's runs of kOlLeaf points. A full run holds more than K other
+// points, so the smallest of the boxes' largest distances bounds the k-th distance; only
+// runs whose box reaches within that bound (with a margin far above float32 rounding) are
+// scanned, eight at a time per wave, a point per lane. (A scan of the whole cloud per query
+// is bound by the caches: 237 us for the 538 stray points of a 314k cloud.)
 template <int K>
-__global__ __launch_bounds__(kOlFarThreads) void k_ol_knn_far(const float4 *__restrict__ spts, const float *__restrict__ pts,
+__global__ __launch_bounds__(kOlFarThreads) void k_ol_knn_far(const float4 *__restrict__ spts, const float4 *__restrict__ boxes,
+                                                    const float *__restrict__ pts,
                                                     int64_t n, int64_t stride, const OlHdr *__restrict__ hdr,
                                                     const uint32_t *__restrict__ defer, float *__restrict__ dmean) {
-    __shared__ float s_l[kOlFarThreads * K];
-    __shared__ float s_t[K];
+    constexpr int NW = kOlFarThreads / 64;
+    __shared__ float s_tau[NW];
+    __shared__ float s_l[NW][K];
     const uint32_t nd = hdr->ndefer;
     const int want = n - 1 < (int64_t)K ? (int)(n - 1) : K;
+    const uint32_t w = threadIdx.x >> 6, l = lane_id();
+    const int64_t leaves = (n + kOlLeaf - 1) / kOlLeaf, full = n / kOlLeaf;
+    const uint32_t last = (uint32_t)n - 1u;
     for (uint32_t q = blockIdx.x; q < nd; q += gridDim.x) {
         const uint32_t i = defer[q];
-        float x, y, z;
-        ol_load(pts, stride, i, x, y, z);
+        float p[3];
+        ol_load(pts, stride, i, p[0], p[1], p[2]);
+        // squared distances to a box: the least and the largest
+        auto reach = [&](int64_t f, float &hi2) {
+            const float4 a = boxes[2 * f], b = boxes[2 * f + 1];
+            const float lo[3] = {a.x, a.y, a.z}, hi[3] = {b.x, b.y, b.z};
+            float l2 = 0.f;
+            hi2 = 0.f;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const float u = lo[k] - p[k], v = p[k] - hi[k];   // both <= 0 inside
+                const float o = fmaxf(fmaxf(u, v), 0.f), e = fmaxf(fabsf(u), fabsf(v));
+                l2 = __builtin_fmaf(o, o, l2);
+                hi2 = __builtin_fmaf(e, e, hi2);
+            }
+            return l2;
+        };
+        float tau = INFINITY;
+        for (int64_t f = threadIdx.x; f < full; f += kOlFarThreads) {
+            float hi2;
+            (void)reach(f, hi2);
+            tau = fminf(tau, hi2);
+        }
+        tau = wave_min(tau);
+        if (l == 0) s_tau[w] = tau;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NW; ++k) tau = fminf(tau, s_tau[k]);
+        tau = tau * (1.f + 2e-5f);   // (inf stays inf)
         float best[K];
 #pragma unroll
         for (int a = 0; a < K; ++a) best[a] = INFINITY;
-        // four loads in flight per iteration (the scan is latency bound otherwise)
-        int64_t j = threadIdx.x;
-        for (; j + 3 * kOlFarThreads < n; j += 4 * kOlFarThreads) {
-            float4 c[4];
+        // neighbouring boxes go to different waves
+        for (int64_t f0 = 0; f0 < leaves; f0 += kOlFarThreads) {
+            const int64_t f = f0 + (int64_t)l * NW + w;
+            float hi2;
+            const bool near = f < leaves && reach(f, hi2) <= tau;
+            uint64_t mm = wave_ballot(near);
+            while (mm) {
+                float4 c[8];
+                uint32_t count = 0;   // (a lane's candidates are in the order of the runs: the last may be short)
 #pragma unroll
-            for (int u = 0; u < 4; ++u) c[u] = spts[j + u * kOlFarThreads];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                if (__float_as_uint(c[u].w) == i) continue;
-                const float ex = c[u].x - x, ey = c[u].y - y, ez = c[u].z - z;
-                ol_insert<K>(best, __builtin_fmaf(ex, ex, __builtin_fmaf(ey, ey, ez * ez)));
-            }
-        }
-        for (; j < n; j += kOlFarThreads) {
-            const float4 c = spts[j];
-            if (__float_as_uint(c.w) == i) continue;
-            const float ex = c.x - x, ey = c.y - y, ez = c.z - z;
-            ol_insert<K>(best, __builtin_fmaf(ex, ex, __builtin_fmaf(ey, ey, ez * ez)));
-        }
-#pragma unroll
-        for (int a = 0; a < K; ++a) s_l[threadIdx.x * K + a] = best[a];
-        __syncthreads();
-        for (int sp = 1; sp < kOlFarThreads; sp <<= 1) {
-            if ((threadIdx.x & (2 * sp - 1)) == 0) {
-                const float *A = s_l + threadIdx.x * K, *B = s_l + (threadIdx.x + sp) * K;
-                float m[K];
-                int ia = 0, ib = 0;
-#pragma unroll
-                for (int a = 0; a < K; ++a) {
-                    const float va = A[ia], vb = B[ib];
-                    const bool ta = va <= vb;
-                    m[a] = ta ? va : vb;
-                    ia += ta ? 1 : 0;
-                    ib += ta ? 0 : 1;
+                for (int u = 0; u < 8; ++u) {
+                    const uint32_t j = (uint32_t)(f0 + (mm ? (int64_t)__builtin_ctzll(mm) * NW + w : 0)) * kOlLeaf + l;
+                    count += mm && j <= last ? 1u : 0u;
+                    mm &= mm - 1;
+                    c[u] = spts[min(j, last)];
                 }
-#pragma unroll
-                for (int a = 0; a < K; ++a) s_l[threadIdx.x * K + a] = m[a];
+                ol_take<K, 8>(best, c, count, i, p[0], p[1], p[2]);
             }
-            __syncthreads();
         }
-        if (threadIdx.x < K) s_t[threadIdx.x] = s_l[threadIdx.x];
+        ol_merge_lanes<K, 64>(best);
+        if (l == 0)
+#pragma unroll
+            for (int a = 0; a < K; ++a) s_l[w][a] = best[a];
         __syncthreads();
-        if (threadIdx.x == 0) {
-            float sum = 0.f;
-            for (int a = 0; a < want; ++a) sum += sqrtf(s_t[a]);
-            dmean[i] = want > 0 ? sum / (float)want : 0.f;
+        if (w == 0) {
+#pragma unroll
+            for (int a = 0; a < K; ++a) best[a] = s_l[l % NW][a];
+            ol_merge_lanes<K, NW>(best);
+            if (l == 0) dmean[i] = ol_mean<K>(best, want);
         }
-        __syncthreads();   // s_l and s_t are reused by the next query
+        __syncthreads();   // s_l and s_tau are reused by the next query
     }
 }
 
@@ -541,28 +596,39 @@ __global__ __launch_bounds__(256) void k_ol_var(const float *__restrict__ dmean,
     }
 }
 
-// 4c. threshold from the summed squares: one wave, a fixed order (the same on every run)
-__global__ __launch_bounds__(64) void k_ol_thr(const float2 *__restrict__ part2, int nblk, int64_t n, float std_ratio,
-                                               OlHdr *__restrict__ hdr) {
-    const FF t = ff_parts(part2, nblk);
-    if (lane_id() != 0) return;
-    const float sigma = sqrtf(fmaxf((t.hi + t.lo) / (float)n, 0.f));
-    hdr->sigma = sigma;
-    hdr->thr = hdr->mu + std_ratio * sigma;
-}
-
-// 4d. keep mask and kept count per workgroup of kOlBlock points
-__global__ __launch_bounds__(256) void k_ol_keep(const float *__restrict__ dmean, int64_t n, const OlHdr *__restrict__ hdr,
+// 4c. threshold from the summed squares (every workgroup the same bits: one wave, a fixed
+// order; workgroup 0 stores it), keep mask and kept count per workgroup of kOlBlock points
+__global__ __launch_bounds__(256) void k_ol_keep(const float *__restrict__ dmean, int64_t n, const float2 *__restrict__ part2,
+                                                 int nblk, float std_ratio, OlHdr *__restrict__ hdr,
                                                  uint8_t *__restrict__ keep, uint32_t *__restrict__ part) {
     __shared__ uint32_t s_w[4];
-    const float thr = hdr->thr;
+    __shared__ float s_thr;
     const int64_t base = (int64_t)blockIdx.x * kOlBlock;
+    float d[kOlItems];
+#pragma unroll
+    for (int k = 0; k < kOlItems; ++k) {
+        const int64_t i = base + k * 256 + threadIdx.x;
+        d[k] = i < n ? dmean[i] : 0.f;
+    }
+    if (threadIdx.x < 64) {
+        const FF t = ff_parts(part2, nblk);
+        if (threadIdx.x == 0) {
+            const float sigma = sqrtf(fmaxf((t.hi + t.lo) / (float)n, 0.f));
+            s_thr = hdr->mu + std_ratio * sigma;
+            if (blockIdx.x == 0) {
+                hdr->sigma = sigma;
+                hdr->thr = s_thr;
+            }
+        }
+    }
+    __syncthreads();
+    const float thr = s_thr;
     uint32_t c = 0;
 #pragma unroll
     for (int k = 0; k < kOlItems; ++k) {
         const int64_t i = base + k * 256 + threadIdx.x;
         if (i < n) {
-            const bool kp = dmean[i] <= thr;
+            const bool kp = d[k] <= thr;
             keep[i] = kp ? 1 : 0;
             c += kp ? 1u : 0u;
         }
@@ -573,14 +639,29 @@ __global__ __launch_bounds__(256) void k_ol_keep(const float *__restrict__ dmean
     if (threadIdx.x == 0) part[blockIdx.x] = s_w[0] + s_w[1] + s_w[2] + s_w[3];
 }
 
-// 4e. compaction of the kept points in input order (offsets from the scanned counts)
+// 4d. compaction of the kept points in input order: from the scanned counts, or (fold, few
+// workgroups) each workgroup sums the counts before its own, and the last one stores the
+// total: one launch fewer
 __global__ __launch_bounds__(256) void k_ol_write(const float *__restrict__ pts, int64_t n, int64_t stride,
-                                                  const uint8_t *__restrict__ keep, const uint32_t *__restrict__ part,
-                                                  float *__restrict__ out, int64_t out_stride) {
+                                                 const uint8_t *__restrict__ keep, const uint32_t *__restrict__ part,
+                                                 float *__restrict__ out, int64_t out_stride, int fold,
+                                                 uint32_t *__restrict__ count) {
     __shared__ uint32_t s_w[4];
     const int64_t base = (int64_t)blockIdx.x * kOlBlock;
     const int l = (int)lane_id(), w = (int)(threadIdx.x >> 6);
-    uint32_t run = part[blockIdx.x];
+    uint32_t run;
+    if (fold) {
+        uint32_t a = 0;
+        for (uint32_t c = threadIdx.x; c < blockIdx.x; c += 256) a += part[c];
+        for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o);
+        if (l == 0) s_w[w] = a;
+        __syncthreads();
+        run = s_w[0] + s_w[1] + s_w[2] + s_w[3];
+        __syncthreads();
+        if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *count = run + part[blockIdx.x];
+    } else {
+        run = part[blockIdx.x];
+    }
 #pragma unroll
     for (int k = 0; k < kOlItems; ++k) {
         const int64_t i = base + k * 256 + threadIdx.x;
@@ -616,7 +697,7 @@ static size_t al(size_t x) { return (x + 255) / 256 * 256; }
 
 // Workspace pieces for n points (offsets in bytes, in this order).
 struct OlLayout {
-    size_t hdr, keys0, vals0, keys1, vals1, hist, shist, scount, ranges, bpart, spart, kpart, defer, slow, spts, total;
+    size_t hdr, keys0, vals0, keys1, vals1, hist, shist, scount, ranges, bpart, spart, kpart, defer, slow, spts, boxes, total;
 };
 
 size_t sort_count_words(uint64_t);
@@ -632,32 +713,39 @@ static OlLayout ol_layout(int64_t n) {
     L.vals0 = take(4 * nn);
     L.keys1 = take(4 * nn);
     L.vals1 = take(4 * nn);
-    L.hist = take(4 * 256 * kMaxPasses);
+    L.hist = take(4 * 256 * kMaxPasses);   // the sort's digit totals
     L.shist = take(4 * 3 * kOlBins);
     L.scount = take(4 * sort_count_words((uint64_t)nn));
-    L.ranges = take(8 * slots);
+    L.ranges = take(4 * (slots + 1));
     L.bpart = take(4 * 6 * kOlRedBlocks);
     L.spart = take(8 * 2 * kOlRedBlocks);   // two float2 partials per reduction workgroup
     L.kpart = take(4 * ((nn + kOlBlock - 1) / kOlBlock + 1));
     L.defer = take(4 * nn);
     L.slow = take(4 * nn);
     L.spts = take(16 * nn);
+    L.boxes = take(32 * ((nn + kOlLeaf - 1) / kOlLeaf));
     L.total = o;
     return L;
 }
 
 size_t outlier_workspace_bytes(int64_t n) { return ol_layout(n).total; }
 
+// slow1, slow2: the lists of the second and third search (nn words each)
 template <int K>
-static void knn_launch(const float *pts, int64_t n, int64_t stride, OlHdr *hdr, const float4 *spts,
-                       const uint2 *ranges, uint32_t *slow, uint32_t *defer, float *dmean, hipStream_t st) {
-    hipLaunchKernelGGL((k_ol_knn<K>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, spts, n, hdr, ranges, slow,
-                       defer, dmean);
-    const unsigned wb = (unsigned)((n + 3) / 4 < kOlWaveBlocks ? (n + 3) / 4 : kOlWaveBlocks);
-    hipLaunchKernelGGL((k_ol_knn_wave<K>), dim3(wb), dim3(256), 0, st, spts, n, hdr, ranges, slow, defer, dmean);
+static void knn_launch(const float *pts, int64_t n, int64_t stride, OlHdr *hdr, const float4 *spts, const float4 *boxes,
+                       const uint32_t *start, uint32_t *slow1, uint32_t *slow2, uint32_t *defer, float *dmean, hipStream_t st) {
+    const auto grid = [&](int lanes, int64_t most) {
+        const int64_t b = (n * lanes + 255) / 256;
+        return dim3((unsigned)(b < most ? b : most));
+    };
+    hipLaunchKernelGGL((k_ol_knn<K, kOlRing1, kOlR1, kOlC1>), grid(kOlR1 * kOlC1, (int64_t)1 << 31), dim3(256), 0, st, spts, n, hdr, start,
+                       nullptr, nullptr, slow1, hdr->nslow, defer, dmean);
+    hipLaunchKernelGGL((k_ol_knn<K, kOlRing2, kOlR2, kOlC2>), grid(kOlR2 * kOlC2, kOlListBlocks), dim3(256), 0, st, spts, n, hdr, start,
+                       slow1, hdr->nslow, slow2, hdr->nslow + 1, defer, dmean);
+    hipLaunchKernelGGL((k_ol_knn<K, kOlRing3, kOlR3, kOlC3>), grid(kOlR3 * kOlC3, kOlListBlocks), dim3(256), 0, st, spts, n, hdr, start,
+                       slow2, hdr->nslow + 1, nullptr, nullptr, defer, dmean);
     const unsigned far = (unsigned)(n < kOlFarBlocks ? n : kOlFarBlocks);
-    hipLaunchKernelGGL((k_ol_knn_far<K>), dim3(far), dim3(kOlFarThreads), 0, st, spts, pts, n, stride, hdr, defer,
-                       dmean);
+    hipLaunchKernelGGL((k_ol_knn_far<K>), dim3(far), dim3(kOlFarThreads), 0, st, spts, boxes, pts, n, stride, hdr, defer, dmean);
 }
 
 // k in {4, 8, 16, 32}: false (nothing launched) otherwise. out may be null (no compaction).
@@ -677,35 +765,36 @@ bool launch_outliers(const float *pts, int64_t n, int64_t stride, int k, float s
     const int bits = outlier_slot_bits(n);
     const uint32_t slots = 1u << bits;
     const int rb = (int)((n + 255) / 256 < kOlRedBlocks ? (n + 255) / 256 : kOlRedBlocks);
-    hipLaunchKernelGGL(k_ol_bbox, dim3(rb), dim3(256), 0, st, pts, n, stride, (float *)(b + L.bpart));
-    hipLaunchKernelGGL(k_ol_bbox_final, dim3(1), dim3(384), 0, st, (const float *)(b + L.bpart), rb, hdr);
-    launch_fill_u32((uint32_t *)(b + L.shist), 0u, 3 * kOlBins, st);
-    hipLaunchKernelGGL(k_ol_hist, dim3(rb), dim3(256), 0, st, pts, n, stride, hdr, (uint32_t *)(b + L.shist));
-    hipLaunchKernelGGL(k_ol_setup, dim3(1), dim3(192), 0, st, (const uint32_t *)(b + L.shist), n, (uint32_t)bits, hdr);
+    uint32_t *shist = (uint32_t *)(b + L.shist);
+    float *bpart = (float *)(b + L.bpart);
+    hipLaunchKernelGGL(k_ol_bbox, dim3(rb), dim3(256), 0, st, pts, n, stride, bpart, shist);
+    const int64_t step = (n + kOlSample - 1) / kOlSample, ns = (n + step - 1) / step;
+    hipLaunchKernelGGL(k_ol_hist, dim3((unsigned)((ns + 255) / 256)), dim3(256), 0, st, pts, n, stride, step, bpart, rb, hdr, shist);
+    hipLaunchKernelGGL(k_ol_setup, dim3(1), dim3(192), 0, st, shist, ns, n, (uint32_t)bits, hdr);
     hipLaunchKernelGGL(k_ol_key, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, pts, n, stride, hdr, k0, v0);
-    launch_fill_u32((uint32_t *)(b + L.hist), 0u, 256 * kMaxPasses, st);
     const int alt = radix_sort_u32(k0, v0, k1, v1, (uint32_t)n, 0u, bits, (uint32_t *)(b + L.hist),
                                    (uint32_t *)(b + L.scount), st);
     const uint32_t *sk = alt ? k1 : k0, *sv = alt ? v1 : v0;
-    uint2 *ranges = (uint2 *)(b + L.ranges);
-    launch_fill_u32((uint32_t *)ranges, 0u, 2 * (int64_t)slots, st);
-    launch_ranges32(sk, (uint32_t)n, ranges, st, nullptr);
-    uint32_t *defer = (uint32_t *)(b + L.defer), *slow = (uint32_t *)(b + L.slow);
-    float4 *spts = (float4 *)(b + L.spts);
-    hipLaunchKernelGGL(k_ol_gather, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, pts, n, stride, sv, spts);
-    if (k == 4) knn_launch<4>(pts, n, stride, hdr, spts, ranges, slow, defer, dmean, st);
-    else if (k == 8) knn_launch<8>(pts, n, stride, hdr, spts, ranges, slow, defer, dmean, st);
-    else if (k == 16) knn_launch<16>(pts, n, stride, hdr, spts, ranges, slow, defer, dmean, st);
-    else knn_launch<32>(pts, n, stride, hdr, spts, ranges, slow, defer, dmean, st);
+    uint32_t *start = (uint32_t *)(b + L.ranges);
+    uint32_t *defer = (uint32_t *)(b + L.defer), *slow1 = (uint32_t *)(b + L.slow);
+    uint32_t *slow2 = alt ? v0 : v1;   // the sort's other value buffer
+    float4 *spts = (float4 *)(b + L.spts), *boxes = (float4 *)(b + L.boxes);
+    const uint32_t sblk = (slots + 256u) / 256u;
+    hipLaunchKernelGGL(k_ol_gather, dim3(sblk + (unsigned)((n + 255) / 256)), dim3(256), 0, st, pts, n, stride, sk, sv, slots, sblk,
+                       start, spts, boxes);
+    if (k == 4) knn_launch<4>(pts, n, stride, hdr, spts, boxes, start, slow1, slow2, defer, dmean, st);
+    else if (k == 8) knn_launch<8>(pts, n, stride, hdr, spts, boxes, start, slow1, slow2, defer, dmean, st);
+    else if (k == 16) knn_launch<16>(pts, n, stride, hdr, spts, boxes, start, slow1, slow2, defer, dmean, st);
+    else knn_launch<32>(pts, n, stride, hdr, spts, boxes, start, slow1, slow2, defer, dmean, st);
     float2 *sp1 = (float2 *)(b + L.spart), *sp2 = sp1 + kOlRedBlocks;
     hipLaunchKernelGGL(k_ol_sum, dim3(rb), dim3(256), 0, st, dmean, n, sp1);
     hipLaunchKernelGGL(k_ol_var, dim3(rb), dim3(256), 0, st, dmean, n, sp1, rb, sp2, hdr);
-    hipLaunchKernelGGL(k_ol_thr, dim3(1), dim3(64), 0, st, sp2, rb, n, std_ratio, hdr);
     const uint32_t nblk = (uint32_t)((n + kOlBlock - 1) / kOlBlock);
-    hipLaunchKernelGGL(k_ol_keep, dim3(nblk), dim3(256), 0, st, dmean, n, hdr, keep, kpart);
-    launch_excl_scan_u32(kpart, nblk, count, st);
+    hipLaunchKernelGGL(k_ol_keep, dim3(nblk), dim3(256), 0, st, dmean, n, sp2, rb, std_ratio, hdr, keep, kpart);
+    const int fold = out && nblk <= kOlScanFold;
+    if (!fold) launch_excl_scan_u32(kpart, nblk, count, st);
     if (out)
-        hipLaunchKernelGGL(k_ol_write, dim3(nblk), dim3(256), 0, st, pts, n, stride, keep, kpart, out, out_stride);
+        hipLaunchKernelGGL(k_ol_write, dim3(nblk), dim3(256), 0, st, pts, n, stride, keep, kpart, out, out_stride, fold, count);
     return true;
 }
 
