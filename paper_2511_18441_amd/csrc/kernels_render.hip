@@ -106,7 +106,8 @@ __global__ __launch_bounds__(256) void k_scan_reduce(const uint32_t *__restrict_
 // the depth range (minimum stored as its complement).
 __global__ __launch_bounds__(1024) void k_scan_top(uint64_t *__restrict__ pk, uint32_t *__restrict__ pv,
                                                    const uint32_t *__restrict__ pzmn, const uint32_t *__restrict__ pzmx,
-                                                   uint32_t nchunks, uint64_t key_capacity, uint32_t *__restrict__ header) {
+                                                   uint32_t nchunks, uint64_t key_capacity, uint32_t *__restrict__ header,
+                                                   HostNote note) {
     __shared__ uint64_t s_wk[16];
     __shared__ uint32_t s_wv[16], s_zmn[16], s_zmx[16];
     const uint32_t t = threadIdx.x, lane = lane_id(), w = t >> 6;
@@ -133,14 +134,7 @@ __global__ __launch_bounds__(1024) void k_scan_top(uint64_t *__restrict__ pk, ui
         for (int k = 1; k < 16; ++k) { zmn = min(zmn, s_zmn[k]); zmx = max(zmx, s_zmx[k]); }
         zmn = min(zmn, s_zmn[0]);
         zmx = max(zmx, s_zmx[0]);
-        header[H_K_LO] = (uint32_t)runk;
-        header[H_K_HI] = (uint32_t)(runk >> 32);
-        header[H_V] = runv;
-        header[H_ZMIN] = runv ? ~zmn : 0u;
-        header[H_ZMAX] = runv ? zmx : 0u;
-        header[H_ZMIN_RAW] = runv ? zmn : 0u;
-        header[H_KEFF] = runk <= key_capacity ? (uint32_t)runk : 0u;
-        header[H_OVERFLOW] = runk > key_capacity ? 1u : 0u;
+        write_counts(header, note, runk, runv, zmn, zmx, key_capacity);
     }
 }
 
@@ -160,6 +154,7 @@ struct ScanFold {
     uint32_t nchunks;
     uint64_t key_capacity;
     uint32_t *header;
+    HostNote note;
 };
 __device__ __forceinline__ void scan_fold_prefix(const uint64_t *__restrict__ pk, const uint32_t *__restrict__ pv,
                                                  const ScanFold &f, uint64_t &pre_k, uint32_t &pre_v) {
@@ -185,14 +180,7 @@ __device__ __forceinline__ void scan_fold_prefix(const uint64_t *__restrict__ pk
         if (t == 0) {
             mn = min(min(s_mn[0], s_mn[1]), min(s_mn[2], s_mn[3]));
             mx = max(max(s_mx[0], s_mx[1]), max(s_mx[2], s_mx[3]));
-            f.header[H_K_LO] = (uint32_t)k;
-            f.header[H_K_HI] = (uint32_t)(k >> 32);
-            f.header[H_V] = v;
-            f.header[H_ZMIN] = v ? ~mn : 0u;
-            f.header[H_ZMAX] = v ? mx : 0u;
-            f.header[H_ZMIN_RAW] = v ? mn : 0u;
-            f.header[H_KEFF] = k <= f.key_capacity ? (uint32_t)k : 0u;
-            f.header[H_OVERFLOW] = k > f.key_capacity ? 1u : 0u;
+            write_counts(f.header, f.note, k, v, mn, mx, f.key_capacity);
         }
         pre_k = 0;
         pre_v = 0;
@@ -793,7 +781,7 @@ void launch_rowscan(uint32_t *cnt, uint32_t chunks, uint32_t chunk_keys, uint32_
 // depth sort's first pass (ScanSort).
 void launch_scan(const uint32_t *cnt, const uint32_t *zbits, uint32_t *off, int64_t n, uint64_t *pk, uint32_t *pv,
                  uint32_t *pzmn, uint32_t *pzmx, uint32_t *dkeys, uint32_t *dvals, uint32_t *hdr, int64_t key_capacity,
-                 hipStream_t st, const ScanEmit *emit, const ScanSort *sort) {
+                 hipStream_t st, const ScanEmit *emit, const ScanSort *sort, const HostNote *hn) {
     if (n <= 0) return;
     const uint32_t nchunks = (uint32_t)((n + kScanChunk - 1) / kScanChunk);
     if (sort) {
@@ -806,9 +794,11 @@ void launch_scan(const uint32_t *cnt, const uint32_t *zbits, uint32_t *off, int6
     }
     // up to 1,024 chunks (4M Gaussians) the down pass scans the partials itself
     const int fold = nchunks <= 1024u;
-    const ScanFold f{pzmn, pzmx, nchunks, (uint64_t)key_capacity, hdr};
+    const HostNote note = hn ? *hn : HostNote{nullptr, 0u};
+    const ScanFold f{pzmn, pzmx, nchunks, (uint64_t)key_capacity, hdr, note};
     if (!fold)
-        hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, st, pk, pv, pzmn, pzmx, nchunks, (uint64_t)key_capacity, hdr);
+        hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, st, pk, pv, pzmn, pzmx, nchunks, (uint64_t)key_capacity, hdr,
+                           note);
     if (emit) {
         const uint32_t nblk = (uint32_t)(((uint64_t)key_capacity + kEmitKeys - 1) / kEmitKeys);
         hipLaunchKernelGGL(k_scan_down<SD_EMIT>, dim3(nchunks), dim3(256), 0, st, cnt, zbits, off, n, pk, pv, dkeys, dvals,

@@ -232,6 +232,37 @@ enum : int {
     H_WORDS = 384
 };
 
+// Where the count scan also leaves the header's first eight words for the host: pinned
+// host memory, one 64-bit word each with the call's sequence number in its upper half, so
+// every word says by itself that it has arrived and no fence (a write-back of the XCD's L2)
+// is needed. words null: not wanted.
+struct HostNote {
+    uint64_t *words;
+    uint32_t seq;
+};
+__device__ __forceinline__ void leave_note(const HostNote &h, const uint32_t (&w)[8]) {
+    if (!h.words) return;
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+        __hip_atomic_store(h.words + k, ((uint64_t)h.seq << 32) | w[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+// The header's results of the count scan (H_K_LO .. H_ZMIN_RAW), also left for the host.
+__device__ __forceinline__ void write_counts(uint32_t *__restrict__ header, const HostNote &note, uint64_t K, uint32_t V,
+                                             uint32_t zmn, uint32_t zmx, uint64_t key_capacity) {
+    uint32_t w[8];
+    w[H_K_LO] = (uint32_t)K;
+    w[H_K_HI] = (uint32_t)(K >> 32);
+    w[H_ZMIN] = V ? ~zmn : 0u;
+    w[H_ZMAX] = V ? zmx : 0u;
+    w[H_V] = V;
+    w[H_KEFF] = K <= key_capacity ? (uint32_t)K : 0u;
+    w[H_OVERFLOW] = K > key_capacity ? 1u : 0u;
+    w[H_ZMIN_RAW] = V ? zmn : 0u;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) header[k] = w[k];
+    leave_note(note, w);
+}
+
 // Per-view description of a batch (device memory): the view's scene, camera and
 // fused recolour, its output, and where its pairs, preprocess blocks and tiles start
 // in the batch's flattened index spaces.
