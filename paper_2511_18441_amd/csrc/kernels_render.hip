@@ -535,6 +535,130 @@ __global__ __launch_bounds__(256) void k_emit_offsets(const uint2 *__restrict__ 
     }
 }
 
+// The count scan, the depth order and the emission offsets of a small scene (n <= N), by
+// counting over all pairs: a Gaussian's place is the number of visible ones before it in
+// (depth, index) order, its key offset the sum of their counts. Every workgroup holds all
+// (depth, count) pairs in LDS and ranks 16 Gaussians: lane = (Gaussian, one of 4 subsets),
+// wave = one of 16 runs of entries, so a 16-byte LDS read serves two entries of four subsets
+// without conflicts. Four VALU instructions a pair (compare, add carry, select, add). Bound
+// by those: n^2 pairs, 17M of them at 4,096 Gaussians. One launch for the 10 of the scan, the
+// passes and the offsets, which cost a launch each and no more at this size: 7.5 us for 48 us
+// at 4,096 Gaussians.
+template <int N>
+__global__ __launch_bounds__(1024) void k_small_order(const uint32_t *__restrict__ cnt, const uint32_t *__restrict__ zbits,
+                                                      const uint2 *__restrict__ rect, uint32_t n, uint64_t key_capacity,
+                                                      uint32_t *__restrict__ off, uint32_t *__restrict__ order,
+                                                      uint2 *__restrict__ srect, uint32_t *__restrict__ eoff,
+                                                      uint32_t *__restrict__ efirst, uint32_t nblk,
+                                                      uint32_t *__restrict__ header, HostNote note) {
+    constexpr int R = N / 1024;
+    __shared__ uint4 s_zc[N / 2];   // entries 2 p, 2 p + 1: (depth bits, count) each; no keys: depth all ones
+    __shared__ uint64_t s_k[16];
+    __shared__ uint32_t s_pre[16], s_v[16], s_mn[16], s_mx[16], s_r[16][16], s_e[16][16];
+    const uint32_t t = threadIdx.x, lane = lane_id(), w = t >> 6;
+    const uint32_t i0 = blockIdx.x * 16u;
+    uint2 *zc = (uint2 *)s_zc;
+    uint32_t c[R], z[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const uint32_t j = min(t + 1024u * r, n - 1);
+        c[r] = cnt[j];
+        z[r] = zbits[j];
+    }
+    uint64_t ksum = 0;
+    uint32_t pre = 0, vsum = 0, mn = 0xffffffffu, mx = 0u;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const uint32_t j = t + 1024u * r;
+        if (j >= n) c[r] = 0u;
+        if (c[r]) {
+            mn = min(mn, z[r]);
+            mx = max(mx, z[r]);
+            ++vsum;
+        } else {
+            z[r] = 0xffffffffu;
+        }
+        ksum += c[r];
+        pre += j < i0 ? c[r] : 0u;
+        zc[j] = make_uint2(z[r], c[r]);
+    }
+    ksum = wave_sum(ksum);
+    pre = wave_sum(pre);
+    if (blockIdx.x == 0) {
+        vsum = wave_sum(vsum);
+        mn = wave_min(mn);
+        mx = wave_max(mx);
+    }
+    if (lane == 0) { s_k[w] = ksum; s_pre[w] = pre; s_v[w] = vsum; s_mn[w] = mn; s_mx[w] = mx; }
+    __syncthreads();
+    uint64_t K = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) K += s_k[k];
+    if (blockIdx.x == 0 && t == 0) {
+        uint32_t V = 0;
+        for (int k = 0; k < 16; ++k) { V += s_v[k]; mn = min(mn, s_mn[k]); mx = max(mx, s_mx[k]); }
+        write_counts(header, note, K, V, mn, mx, key_capacity);
+    }
+    const uint32_t i = i0 + (lane & 15u), sub = lane >> 4;   // i < N: the padded entries have no keys
+    const uint2 own = zc[i];
+    // run of the wave: steps of 8 entries, two per subset; an entry before i counts at equal
+    // depth too. Only the two steps that hold i0 .. i0 + 15 need a look at each index.
+    const uint32_t steps = (n + 127u) / 128u, s0 = w * steps, s1 = s0 + steps;
+    const uint32_t a = min(max(i0 / 8u, s0), s1), b = min(max(i0 / 8u + 2u, s0), s1);
+    uint32_t rank = 0, sum = 0;
+    auto pair = [&](uint32_t z0, uint32_t z1, const uint4 &q) {
+        rank += q.x < z0 ? 1u : 0u;
+        sum += q.x < z0 ? q.y : 0u;
+        rank += q.z < z1 ? 1u : 0u;
+        sum += q.z < z1 ? q.w : 0u;
+    };
+#pragma unroll 4
+    for (uint32_t k = s0; k < a; ++k) pair(own.x + 1u, own.x + 1u, s_zc[4u * k + sub]);
+    for (uint32_t k = a; k < b; ++k) {
+        const uint32_t j = 8u * k + 2u * sub;
+        pair(own.x + (j < i ? 1u : 0u), own.x + (j + 1u < i ? 1u : 0u), s_zc[4u * k + sub]);
+    }
+#pragma unroll 4
+    for (uint32_t k = b; k < s1; ++k) pair(own.x, own.x, s_zc[4u * k + sub]);
+    rank += __shfl_xor(rank, 16);
+    sum += __shfl_xor(sum, 16);
+    rank += __shfl_xor(rank, 32);
+    sum += __shfl_xor(sum, 32);
+    if (sub == 0) { s_r[w][lane] = rank; s_e[w][lane] = sum; }
+    __syncthreads();
+    if (t >= 16 || i >= n) return;
+    uint32_t o = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) o += s_pre[k];
+    for (uint32_t k = 0; k < t; ++k) o += zc[i0 + k].y;
+    off[i] = o;
+    if (K > key_capacity || own.y == 0) return;   // overflow: nothing is emitted
+    rank = sum = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) { rank += s_r[k][t]; sum += s_e[k][t]; }
+    order[rank] = i;
+    srect[rank] = rect[i];
+    eoff[rank] = sum;
+    for (uint32_t k = (sum + kEmitKeys - 1) / kEmitKeys; k < nblk && k * kEmitKeys < sum + own.y; ++k) efirst[k] = rank;
+}
+
+// n <= kSmallScene; the outputs of launch_scan and of launch_emit_sorted's offsets pass
+void launch_small_order(const uint32_t *cnt, const uint32_t *zbits, const uint2 *rect, uint32_t n, int64_t key_capacity,
+                        uint32_t *off, uint32_t *order, uint2 *srect, uint32_t *eoff, uint32_t *efirst, uint32_t *hdr,
+                        const HostNote &note, hipStream_t st) {
+    if (n == 0) return;
+    const uint32_t nblk = (uint32_t)(((uint64_t)key_capacity + kEmitKeys - 1) / kEmitKeys);
+    const dim3 g((n + 15u) / 16u);
+#define RECOGS_SMALL(N)                                                                                                 \
+    hipLaunchKernelGGL(k_small_order<N>, g, dim3(1024), 0, st, cnt, zbits, rect, n, (uint64_t)key_capacity, off, order, \
+                       srect, eoff, efirst, nblk, hdr, note)
+    if (n <= 2048) RECOGS_SMALL(2048);
+    else if (n <= 4096) RECOGS_SMALL(4096);
+    else if (n <= 8192) RECOGS_SMALL(8192);
+    else RECOGS_SMALL(12288);
+#undef RECOGS_SMALL
+}
+
 // exclusive max-scan over the workgroup of one value per thread (256 threads; 0 for thread 0)
 __device__ __forceinline__ uint32_t block_excl_max256(uint32_t v, uint32_t *s_w) {
     const uint32_t lane = lane_id(), w = threadIdx.x >> 6;
@@ -827,6 +951,7 @@ void launch_emit_compacted(const uint32_t *order, uint32_t V, const uint2 *srect
 }
 
 // V is the count or, with dynV, its upper bound; hdr (optional) supplies the overflow flag.
+// folded 2: the offsets are in eoff / efirst already (k_small_order), only the keys are left.
 void launch_emit_sorted(const uint32_t *order, uint32_t V, const uint2 *rect, uint2 *srect, int tiles_x,
                         uint32_t *esum, uint32_t *eoff, uint32_t *efirst, uint32_t K, uint32_t *tkeys, uint32_t *tvals,
                         hipStream_t st, const uint32_t *dynV, const uint32_t *dynK, const uint32_t *hdr,
@@ -839,8 +964,11 @@ void launch_emit_sorted(const uint32_t *order, uint32_t V, const uint2 *rect, ui
     if (!folded) hipLaunchKernelGGL(k_emit_reduce, dim3(chunks), dim3(256), 0, st, order, V, rect, srect, esum, dynV);
     // up to 2,048 chunks (2M depth-ordered Gaussians) the offsets pass scans the sums itself
     const int fold = chunks <= 2048u;
-    if (!fold) hipLaunchKernelGGL(k_scan_top_u32, dim3(1), dim3(1024), 0, st, esum, chunks);
-    hipLaunchKernelGGL(k_emit_offsets, dim3(chunks), dim3(256), 0, st, srect, V, esum, eoff, efirst, nblk, dynV, ovf, fold);
+    if (folded < 2) {
+        if (!fold) hipLaunchKernelGGL(k_scan_top_u32, dim3(1), dim3(1024), 0, st, esum, chunks);
+        hipLaunchKernelGGL(k_emit_offsets, dim3(chunks), dim3(256), 0, st, srect, V, esum, eoff, efirst, nblk, dynV, ovf,
+                           fold);
+    }
     const KeyCount none{nullptr, 0u, 0};
     hipLaunchKernelGGL(k_emit_down, dim3(nblk), dim3(256), 0, st, order, V, K, srect, eoff, efirst, tiles_x, tkeys, tvals,
                        dynV, dynK, ovf, vtab, nviews, kc ? *kc : none);

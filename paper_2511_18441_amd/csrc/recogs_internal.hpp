@@ -309,6 +309,9 @@ constexpr uint32_t kEmitKeys = 2048;                 // keys per workgroup of k_
 constexpr int kScanItems = 16;                       // counts per thread of the scan
 constexpr int kScanChunk = 256 * kScanItems;         // counts per scan workgroup
 constexpr int kMaxPasses = 8;
+// Scenes of at most this many Gaussians get their depth order and emission offsets by
+// counting over all pairs (k_small_order) instead of by the scan and the radix passes.
+constexpr int kSmallScene = 12288;
 constexpr int kEmitItems = 4;                        // depth-ordered Gaussians per thread (emission reduce / offsets)
 constexpr int kEmitChunk = 256 * kEmitItems;         // depth-ordered Gaussians per emission workgroup
 
