@@ -131,7 +131,7 @@ __global__ __launch_bounds__(64) void k_blend_region_persistent(const ViewDev *_
                                                                const uint32_t *__restrict__ order, uint32_t ntiles,
                                                                uint32_t *__restrict__ xqueue) {
     constexpr uint32_t NR = (TW / 8) * (TH / (8 * PPT));
-    __shared__ BlendRec sm[64];
+    __shared__ BlendRing sm;
     const uint32_t x = blockIdx.x & 7u;
     const uint32_t nitems = (ntiles > x ? (ntiles - x + 7u) / 8u : 0u) * NR;
     uint32_t *q = xqueue + 32u * x;
@@ -184,8 +184,11 @@ static void persistent_one(uint32_t grid, hipStream_t st, const ViewDev *views, 
                            const uint32_t *vals, const SplatRec *rec, const uint32_t *order, uint32_t ntiles,
                            uint32_t *queue) {
     if constexpr (region_shape(TW, TH, PPT)) {
-        // 32 one-wave workgroups per CU (grid = CUs x 8); `queue` is the header's H_QUEUE word
-        hipLaunchKernelGGL((k_blend_region_persistent<TW, TH, PPT>), dim3(grid * 4), dim3(64), 0, st, views, nviews, ranges,
+        // 20 one-wave workgroups per CU (grid = CUs x 8): 32 views of 8 scenes took 2350 us with
+        // 32, 2136 with 24, 2108 with 20, 2139 with 16, 2881 with 8 (a full CU adds no issue
+        // slots and spreads its waves over more lists than the caches hold); `queue` is the
+        // header's H_QUEUE word
+        hipLaunchKernelGGL((k_blend_region_persistent<TW, TH, PPT>), dim3(grid * 5 / 2), dim3(64), 0, st, views, nviews, ranges,
                            vals, rec, order, ntiles, queue + (H_XQUEUE - H_QUEUE));
     } else {
         hipLaunchKernelGGL((k_blend_persistent<TW, TH, PPT>), dim3(grid), dim3(TW * TH / PPT), 0, st, views, nviews, ranges,

@@ -848,7 +848,7 @@ __global__ __launch_bounds__(64) void k_blend_region(const uint2 *__restrict__ r
                                                     uint32_t *__restrict__ nproc, const uint32_t *__restrict__ zbits,
                                                     float tau, float *__restrict__ depth) {
     constexpr uint32_t NR = (TW / 8) * (TH / (8 * PPT));
-    __shared__ BlendRec sm[64];
+    __shared__ BlendRing sm;
     const uint32_t b = blockIdx.x, j = b >> 3;
     const uint32_t tile = (j / NR) * 8u + (b & 7u);
     if (tile >= ntiles) return;

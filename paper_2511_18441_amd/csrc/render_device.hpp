@@ -342,46 +342,169 @@ __device__ __forceinline__ void blend_tile(int tile, uint2 rg, const uint32_t *_
     }
 }
 
+// LDS of a region wave: a ring of the records it takes, in groups of four. A chunk of 64 list
+// entries leaves at most 3 records of an unfinished group behind, so 67 slots are live at
+// once; 96 slots are 4.5 KB, and 32 one-wave workgroups fit in a CU's LDS.
+constexpr uint32_t kRing = 96;
+struct BlendGroup {
+    struct {
+        float4 r1;       // base-2 conic terms and log2 sigma
+        float2 uv, pad;  // projected centre
+    } geo[4];
+    float col[3][4];     // [component][record]
+    uint32_t pos[4];     // 1-based list position (STATE / DEPTH)
+};
+struct BlendRing {
+    BlendGroup g[kRing / 4];
+};
+template <bool POS>
+__device__ __forceinline__ void ring_put(BlendRing &sm, uint32_t slot, const float4 &r0, const float4 &r1, const float4 &r2,
+                                         uint32_t pos) {
+    const uint32_t r = slot & 3u;
+    BlendGroup &g = *reinterpret_cast<BlendGroup *>(reinterpret_cast<char *>(sm.g) + __umul24(slot >> 2, sizeof(BlendGroup)));
+    g.geo[r].r1 = r1;
+    g.geo[r].uv = make_float2(r0.x, r0.y);
+    g.col[0][r] = r2.x;
+    g.col[1][r] = r2.y;
+    g.col[2][r] = r2.z;
+    if constexpr (POS) g.pos[r] = pos;
+}
+
+// Four records (one group of the ring) applied to the wave's pixels, front to back:
+// blend_step's arithmetic on every pixel, in the same order, the same bits.
+// The exponents are evaluated with one record per 16-lane row: row g reads record g and
+// takes the 64 pixels' columns l & 7 at four rows each, so a record's geometry is read into 16
+// lanes instead of 64 and the four pixels of a lane share dx. Four swaps of rows then give
+// every lane its own pixel's four alphas (0 below the threshold: such a record changes
+// nothing, C + r 0 == C and T - 0 T == T, exactly).
+// T is the transmittance while compositing and 0 once stopped (Tf keeps the final value,
+// live the pixels still compositing). T only falls, so one test after the fourth record shows
+// that none of the four stopped a pixel; only otherwise are the records from the stop on taken
+// out of the weights.
+// Bound by vector issue: 1M Gaussians at 1920 x 1080, 32 x 32 tiles, 84.3M -> 79.4M VALU issue
+// slots and 11.1M -> 5.1M LDS instructions per launch against one record at a time, 136 ->
+// 128 us; at 1280 x 720 with STATE 96.6 -> 84.5 us; where waves are few and the chain's latency
+// counts (4,096 Gaussians at 128 x 128), 44.6 -> 31.4 us. The colours by 4x4x1 matrix
+// products instead of the twelve FMAs (the same bits) took 147 us.
+template <int PPT, bool STATE, bool DEPTH>
+__device__ __forceinline__ void blend_group(const BlendGroup &g, const float (*pyg)[4], float pxg, float *T, float *Tf,
+                                            uint64_t *live, float *C0, float *C1, float *C2, uint32_t *last,
+                                            uint32_t *cross, float tau) {
+#pragma clang fp contract(off)
+    const uint32_t row = lane_id() >> 4;
+    const float4 r1 = g.geo[row].r1;
+    const float2 uv = g.geo[row].uv;
+    float cr[4], cg[4], cb[4];
+    uint32_t pos[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        cr[r] = g.col[0][r];
+        cg[r] = g.col[1][r];
+        cb[r] = g.col[2][r];
+        pos[r] = (STATE || DEPTH) ? g.pos[r] : 0u;
+    }
+    const ExpRow er = exp_row(r1, pxg - uv.x);
+    float w[PPT][4], U[PPT][5];
+    uint64_t low = 0;
+#pragma unroll
+    for (int j = 0; j < PPT; ++j) {
+        float x[4], a[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const float e = exp_at(er, r1, pyg[j][s] - uv.y);
+            const float al = fminf(kAlphaMax, __builtin_amdgcn_exp2f(e));
+            x[s] = e < kLog2AlphaMin ? 0.f : al;
+        }
+        // x[s] of row g: record g at the pixel of row s -> a[r] of row s: record r at its pixel
+        fold_swap32(x[0], x[2], x[0], x[2]);
+        fold_swap32(x[1], x[3], x[1], x[3]);
+        fold_swap16(x[0], x[1], a[0], a[1]);
+        fold_swap16(x[2], x[3], a[2], a[3]);
+        U[j][0] = T[j];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            w[j][r] = a[r] * U[j][r];
+            U[j][r + 1] = __builtin_fmaf(-a[r], U[j][r], U[j][r]);   // T (1 - alpha), rounded once
+        }
+        low |= wave_ballot(U[j][4] < kTMin) & live[j];
+        T[j] = U[j][4];
+    }
+    if (low) {
+#pragma unroll
+        for (int j = 0; j < PPT; ++j) {
+            float f = 0.f;   // T before the record that stopped the pixel in this group
+#pragma unroll
+            for (int r = 3; r >= 0; --r) {
+                const bool s = U[j][r + 1] < kTMin;
+                w[j][r] = s ? 0.f : w[j][r];
+                f = s ? U[j][r] : f;
+                if (r == 3) T[j] = s ? 0.f : T[j];
+            }
+            Tf[j] = f > 0.f ? f : Tf[j];   // (f is 0 for a pixel stopped before)
+            live[j] = wave_ballot(T[j] > 0.f);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < PPT; ++j) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            C0[j] = __builtin_fmaf(cr[r], w[j][r], C0[j]);
+            C1[j] = __builtin_fmaf(cg[r], w[j][r], C1[j]);
+            C2[j] = __builtin_fmaf(cb[r], w[j][r], C2[j]);
+            if constexpr (STATE) last[j] = w[j][r] > 0.f ? pos[r] : last[j];
+            if constexpr (DEPTH) cross[j] = (w[j][r] > 0.f && U[j][r + 1] < tau && U[j][r] >= tau) ? pos[r] : cross[j];
+        }
+    }
+}
+
 // Region form of the same blend: one wave, alone in its workgroup, composites the
 // 8 x 8*PPT pixel region `sub` of tile `tile` (regions numbered row-major, TW / 8 per
 // row). It reads the tile's whole list 64 records at a time, one per lane, and takes
-// those that pass region_hit for its own region, in list order (compacted into the
-// first LDS slots, with their list positions where STATE or DEPTH needs them). No barrier couples
+// those that pass region_hit for its own region, in list order, through a ring in LDS, from
+// which they are composited four at a time (blend_group). No barrier couples
 // the regions of a tile: a region whose pixels have all stopped retires at once, so
 // the sort tile can be larger than the region without the early-stopped pixels
 // holding the rest. The per-pixel arithmetic and the list positions kept with STATE
 // are those of blend_tile, so both forms give bit-identical outputs. With DEPTH the
 // rough depth map (Sec. 3.2) is written too: per pixel, the float32 depth (zbits, per
 // record) of the splat whose blending takes T below tau, 0 where none does.
-constexpr int kRegionUnroll = 4;
-
 template <int TW, int TH, int PPT, bool STATE, bool DEPTH = false>
 __device__ __forceinline__ void blend_region(int tile, int sub, uint2 rg, const uint32_t *__restrict__ vals,
                                              const SplatRec *__restrict__ rec, int W, int H, int tiles_x, float bg0,
                                              float bg1, float bg2, float *__restrict__ image, int chw,
-                                             float *__restrict__ finalT, uint32_t *__restrict__ nproc,
-                                             BlendRec *sm /* [64] */, const uint32_t *__restrict__ zbits = nullptr,
-                                             float tau = 0.f, float *__restrict__ depth = nullptr) {
+                                             float *__restrict__ finalT, uint32_t *__restrict__ nproc, BlendRing &sm,
+                                             const uint32_t *__restrict__ zbits = nullptr, float tau = 0.f,
+                                             float *__restrict__ depth = nullptr) {
 #pragma clang fp contract(off)
     static_assert(TW % 8 == 0 && TH % (8 * PPT) == 0, "regions of 8 x 8*PPT pixels");
     const int l = (int)lane_id();
     const int bx = (tile % tiles_x) * TW + (sub % (TW / 8)) * 8;
     const int by = (tile / tiles_x) * TH + (sub / (TW / 8)) * 8 * PPT;
     const int px = bx + (l & 7);
-    const float pxc = (float)px + 0.5f;
     const float x0 = (float)bx + 0.5f, x1 = x0 + 7.f;
     const float y0 = (float)by + 0.5f, y1 = y0 + (float)(8 * PPT - 1);
-    float pyc[PPT], T[PPT], C0[PPT], C1[PPT], C2[PPT];
+    float T[PPT], Tf[PPT], C0[PPT], C1[PPT], C2[PPT], pyg[PPT][4];
+    uint64_t live[PPT];
     uint32_t last[PPT], cross[PPT];
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
         const int py = by + (l >> 3) * PPT + j;
-        pyc[j] = (float)py + 0.5f;
-        T[j] = (px < W && py < H) ? 1.f : -1.f;  // pixels outside the image start stopped
-        C0[j] = C1[j] = C2[j] = 0.f;
+        T[j] = (px < W && py < H) ? 1.f : 0.f;  // pixels outside the image start stopped
+        live[j] = wave_ballot(T[j] > 0.f);
+        Tf[j] = C0[j] = C1[j] = C2[j] = 0.f;
         last[j] = 0;
         cross[j] = 0;
+        // the pixel of lane 16 s + (l & 15): the same column in every 16-lane row
+#pragma unroll
+        for (int s = 0; s < 4; ++s) pyg[j][s] = (float)(by + (2 * s + ((l >> 3) & 1)) * PPT + j) + 0.5f;
     }
+    const float pxg = (float)px + 0.5f;
+    auto any_live = [&]() {
+        uint64_t m = 0;
+#pragma unroll
+        for (int j = 0; j < PPT; ++j) m |= live[j];
+        return m != 0;
+    };
     // Software pipeline over chunks of 64 list entries (one per lane): the records of
     // chunk c are in registers while chunk c - 1 is composited, and the list values of
     // chunk c + 1 are on their way, so the two dependent loads are off the critical path.
@@ -395,22 +518,17 @@ __device__ __forceinline__ void blend_region(int tile, int sub, uint2 rg, const 
         }
         if (k + 64u < rg.y) vnext = vals[k + 64u];
     }
-    for (uint32_t start = rg.x; start < rg.y; start += 64) {
-        bool alive = false;
-#pragma unroll
-        for (int j = 0; j < PPT; ++j) alive = alive || T[j] > 0.f;
-        if (!wave_ballot(alive)) break;
+    uint32_t head = 0, left = 0;   // of the ring: first slot and number of records waiting (wave-uniform)
+    for (uint32_t start = rg.x; start < rg.y && any_live(); start += 64) {
         const bool hit = start + (uint32_t)l < rg.y && region_hit(p0, p1, x0, x1, y0, y1);
         const uint64_t mm = wave_ballot(hit);
-        if (hit) {   // compacted in list order: slot = passing lanes below this one
-            const uint32_t slot = rank_below(mm);
-            sm[slot].uv = make_float2(p0.x, p0.y);
-            sm[slot].r1 = p1;
-            sm[slot].rgb = p2;
-            if constexpr (STATE || DEPTH) sm[slot].pad = start + 1u - rg.x + (uint32_t)l;   // 1-based list position
+        const uint32_t tail = head + left;   // < 2 kRing
+        if (hit) {   // in list order: passing lanes below this one; 1-based list position
+            uint32_t slot = tail + rank_below(mm);
+            slot = min(slot, slot - kRing);   // slot mod kRing (the difference wraps below kRing)
+            ring_put<STATE || DEPTH>(sm, slot, p0, p1, p2, start + 1u - rg.x + (uint32_t)l);
         }
-        const int nh = (int)__builtin_popcountll(mm);
-        wave_sync();   // the lanes' LDS writes before any lane reads
+        left += (uint32_t)__builtin_popcountll(mm);
         {
             const uint32_t k = start + 64u + (uint32_t)l;
             if (k < rg.y) {
@@ -419,23 +537,22 @@ __device__ __forceinline__ void blend_region(int tile, int sub, uint2 rg, const 
             }
             if (k + 64u < rg.y) vnext = vals[k + 64u];
         }
-        // kRegionUnroll records per liveness check: consecutive slots, so their LDS
-        // addresses are one base plus immediate offsets
-        for (int q = 0; q < nh; q += kRegionUnroll) {
-            bool live = false;
-#pragma unroll
-            for (int j = 0; j < PPT; ++j) live = live || T[j] > 0.f;
-            if (!wave_ballot(live)) break;
-            // the group's LDS base as an opaque vector value: kept in one register for
-            // the group (a copy per step otherwise), the records at immediate offsets
-            uint32_t off = (uint32_t)q * (uint32_t)sizeof(BlendRec);
-            asm volatile("" : "+v"(off));
-            const BlendRec *g = reinterpret_cast<const BlendRec *>(reinterpret_cast<const char *>(sm) + off);
-#pragma unroll
-            for (int u = 0; u < kRegionUnroll; ++u)
-                if (q + u < nh)
-                    blend_step<PPT, STATE, DEPTH>(g[u], pxc, pyc, T, C0, C1, C2, last, (STATE || DEPTH) ? g[u].pad : 0u,
-                                                  cross, tau);
+        if (start + 64u >= rg.y) {   // the last chunk: the last group filled up with records of alpha 0
+            const uint32_t pad = (0u - left) & 3u;
+            if ((uint32_t)l < pad) {
+                uint32_t slot = head + left + (uint32_t)l;
+                slot = min(slot, slot - kRing);
+                const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+                ring_put<false>(sm, slot, zero, make_float4(0.f, 0.f, 0.f, -1e30f), zero, 0u);
+            }
+            left += pad;
+        }
+        wave_sync();   // the lanes' LDS writes before any lane reads
+        while (left >= 4u) {
+            blend_group<PPT, STATE, DEPTH>(sm.g[head >> 2], pyg, pxg, T, Tf, live, C0, C1, C2, last, cross, tau);
+            if (!any_live()) break;
+            left -= 4u;
+            head = head + 4u == kRing ? 0u : head + 4u;
         }
         wave_sync();   // all reads of this chunk before the next chunk's writes
     }
@@ -444,11 +561,11 @@ __device__ __forceinline__ void blend_region(int tile, int sub, uint2 rg, const 
         const int py = by + (l >> 3) * PPT + j;
         if (px < W && py < H) {
             const int64_t p = (int64_t)py * W + px;
-            const float Tf = fabsf(T[j]);
-            store_pixel(image, p, (int64_t)W * H, chw, __builtin_fmaf(Tf, bg0, C0[j]), __builtin_fmaf(Tf, bg1, C1[j]),
-                        __builtin_fmaf(Tf, bg2, C2[j]));
+            const float Te = T[j] > 0.f ? T[j] : Tf[j];
+            store_pixel(image, p, (int64_t)W * H, chw, __builtin_fmaf(Te, bg0, C0[j]), __builtin_fmaf(Te, bg1, C1[j]),
+                        __builtin_fmaf(Te, bg2, C2[j]));
             if constexpr (STATE) {
-                finalT[p] = Tf;
+                finalT[p] = Te;
                 nproc[p] = last[j];
             }
             if constexpr (DEPTH) depth[p] = cross[j] ? __uint_as_float(zbits[vals[rg.x + cross[j] - 1u]]) : 0.f;
