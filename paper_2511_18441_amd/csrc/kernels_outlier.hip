@@ -33,7 +33,7 @@
 namespace recogs {
 
 int radix_sort_u32(uint32_t *, uint32_t *, uint32_t *, uint32_t *, uint32_t, uint32_t, int, uint32_t *, uint32_t *,
-                   hipStream_t, const EmitFold * = nullptr, bool = false);
+                   hipStream_t, bool = false);
 void launch_excl_scan_u32(uint32_t *, uint32_t, uint32_t *, hipStream_t);
 
 constexpr int kOlBins = 1024;

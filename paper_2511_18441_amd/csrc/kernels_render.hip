@@ -50,7 +50,7 @@ __device__ __forceinline__ T block_excl_scan(T v, T *s_w, T &total) {
     return pre + inc - v;
 }
 
-// HIST: also the chunk's counts of the low 8 depth bits (ScanSort), dcnt[d * nchunks + chunk]
+// HIST: also the chunk's counts of the low depth bits (ScanSort), dcnt[d * nchunks + chunk]
 template <bool HIST>
 __global__ __launch_bounds__(256) void k_scan_reduce(const uint32_t *__restrict__ cnt, const uint32_t *__restrict__ zbits,
                                                      int64_t n, uint64_t *__restrict__ pk, uint32_t *__restrict__ pv,
@@ -58,10 +58,11 @@ __global__ __launch_bounds__(256) void k_scan_reduce(const uint32_t *__restrict_
                                                      uint32_t *__restrict__ dcnt, uint32_t nchunks) {
     __shared__ uint64_t s_k[4];
     __shared__ uint32_t s_v[4], s_zmn[4], s_zmx[4];
-    __shared__ uint32_t s_h[HIST ? 256 : 1];
+    __shared__ uint32_t s_h[HIST ? kScanDigits : 1];
     const uint32_t lane = lane_id(), w = threadIdx.x >> 6;
     if constexpr (HIST) {
-        s_h[threadIdx.x] = 0u;
+#pragma unroll
+        for (uint32_t d = threadIdx.x; d < kScanDigits; d += 256) s_h[d] = 0u;
         __syncthreads();
     }
     // striped (coalesced): only sums, minima and maxima are taken here
@@ -84,7 +85,7 @@ __global__ __launch_bounds__(256) void k_scan_reduce(const uint32_t *__restrict_
             zmn = min(zmn, z);
             zmx = max(zmx, z);
             ++vsum;
-            if constexpr (HIST) atomicAdd(&s_h[z & 255u], 1u);
+            if constexpr (HIST) atomicAdd(&s_h[z & (kScanDigits - 1u)], 1u);
         }
     }
     tsum = wave_sum(tsum);
@@ -99,7 +100,10 @@ __global__ __launch_bounds__(256) void k_scan_reduce(const uint32_t *__restrict_
         pzmn[blockIdx.x] = min(min(s_zmn[0], s_zmn[1]), min(s_zmn[2], s_zmn[3]));
         pzmx[blockIdx.x] = max(max(s_zmx[0], s_zmx[1]), max(s_zmx[2], s_zmx[3]));
     }
-    if constexpr (HIST) dcnt[(size_t)threadIdx.x * nchunks + blockIdx.x] = s_h[threadIdx.x];
+    if constexpr (HIST) {
+#pragma unroll
+        for (uint32_t d = threadIdx.x; d < kScanDigits; d += 256) dcnt[(size_t)d * nchunks + blockIdx.x] = s_h[d];
+    }
 }
 
 // One workgroup: exclusive scans of the chunk partials in place; header gets K, V and
@@ -192,18 +196,15 @@ __device__ __forceinline__ void scan_fold_prefix(const uint64_t *__restrict__ pk
 }
 
 // MODE: SD_COMPACT writes the (depth bits, index) pairs of the Gaussians with keys
-// compacted in index order; SD_EMIT the tile-first order's compaction (ScanEmit);
-// SD_SORT the pairs ordered by their low 8 depth bits (ScanSort: the depth sort's
-// first pass, ranked as k_radix_down ranks, from the digit offsets in dcnt).
-enum : int { SD_COMPACT = 0, SD_EMIT = 1, SD_SORT = 2 };
+// compacted in index order; SD_EMIT the tile-first order's compaction (ScanEmit).
+enum : int { SD_COMPACT = 0, SD_EMIT = 1 };
 template <int MODE>
 __global__ __launch_bounds__(256) void k_scan_down(const uint32_t *__restrict__ cnt, const uint32_t *__restrict__ zbits,
                                                    uint32_t *__restrict__ off, int64_t n, const uint64_t *__restrict__ pk,
                                                    const uint32_t *__restrict__ pv, uint32_t *__restrict__ dkeys,
                                                    uint32_t *__restrict__ dvals, const uint2 *__restrict__ rect,
                                                    uint2 *__restrict__ srect, uint32_t *__restrict__ eoff,
-                                                   uint32_t *__restrict__ efirst, uint32_t nblk, int fold, ScanFold f,
-                                                   const uint32_t *__restrict__ dcnt, const uint32_t *__restrict__ dtot) {
+                                                   uint32_t *__restrict__ efirst, uint32_t nblk, int fold, ScanFold f) {
     constexpr bool EMIT = MODE == SD_EMIT;
     __shared__ uint64_t s_wk[4];
     __shared__ uint32_t s_wv[4];
@@ -211,33 +212,10 @@ __global__ __launch_bounds__(256) void k_scan_down(const uint32_t *__restrict__ 
     __shared__ uint32_t s_dk[kScanChunk], s_dv[kScanChunk];
     const int t = threadIdx.x;
     const int64_t c0 = (int64_t)blockIdx.x * kScanChunk;
-    // SD_SORT loads the counts wave-striped (wave w: entries 1024 w + 64 r + lane, the
-    // order its ranking takes them in) and keeps them, with the depth bits and the digit
-    // offsets, in registers: every global load of the workgroup is issued here
-    uint32_t cw[MODE == SD_SORT ? kScanItems : 1], zk[MODE == SD_SORT ? kScanItems : 1];
-    uint32_t dtot_t = 0, dcnt_t = 0;
-    if constexpr (MODE == SD_SORT) {
-        const uint32_t wl = (uint32_t)t >> 6, ln = lane_id();
 #pragma unroll
-        for (int r = 0; r < kScanItems; ++r) {
-            const int i = (int)(wl * (64 * kScanItems) + r * 64 + ln);
-            cw[r] = (c0 + i < n) ? cnt[c0 + i] : 0u;
-        }
-#pragma unroll
-        for (int r = 0; r < kScanItems; ++r) {
-            const int i = (int)(wl * (64 * kScanItems) + r * 64 + ln);
-            zk[r] = (c0 + i < n) ? zbits[c0 + i] : 0u;
-        }
-        dtot_t = dtot[t];
-        dcnt_t = dcnt[(size_t)t * gridDim.x + blockIdx.x];
-#pragma unroll
-        for (int r = 0; r < kScanItems; ++r) s_a[scan_pad((int)(wl * (64 * kScanItems) + r * 64 + ln))] = cw[r];
-    } else {
-#pragma unroll
-        for (int k = 0; k < kScanItems; ++k) {
-            const int i = k * 256 + t;
-            s_a[scan_pad(i)] = (c0 + i < n) ? cnt[c0 + i] : 0u;
-        }
+    for (int k = 0; k < kScanItems; ++k) {
+        const int i = k * 256 + t;
+        s_a[scan_pad(i)] = (c0 + i < n) ? cnt[c0 + i] : 0u;
     }
     __syncthreads();
     uint32_t v[kScanItems];
@@ -282,7 +260,7 @@ __global__ __launch_bounds__(256) void k_scan_down(const uint32_t *__restrict__ 
             srect[vbase + j] = rect[s_dv[j]];   // within the chunk's 4,096 Gaussians: few lines
         }
         __syncthreads();
-    } else if constexpr (MODE == SD_COMPACT) {
+    } else {
 #pragma unroll
         for (int k = 0; k < kScanItems; ++k) {
             const int i = k * 256 + t;
@@ -299,68 +277,6 @@ __global__ __launch_bounds__(256) void k_scan_down(const uint32_t *__restrict__ 
             }
         }
         __syncthreads();
-    } else {
-        // wave w ranks Gaussians [1024 w, 1024 w + 1024) of the chunk, 64 per round, so
-        // the ranks follow index order; then digit order through LDS (s_dk, s_dv) and out
-        // as contiguous runs at the digits' offsets
-        __shared__ uint32_t s_whist[4][256];
-        __shared__ uint32_t s_gbase[256], s_lstart[256];
-        const uint32_t lane = lane_id(), w = (uint32_t)t >> 6;
-        for (int i = t; i < 4 * 256; i += 256) (&s_whist[0][0])[i] = 0u;
-        {
-            uint32_t all;
-            const uint32_t dbase = block_excl_scan<uint32_t, 4>(dtot_t, s_wv, all);
-            s_gbase[t] = dbase + dcnt_t;
-        }
-        __syncthreads();
-        uint32_t rk[kScanItems], vm = 0u;
-#pragma unroll
-        for (int r = 0; r < kScanItems; ++r) vm |= (cw[r] != 0u ? 1u : 0u) << r;
-#pragma unroll
-        for (int r = 0; r < kScanItems; ++r) {
-            const bool valid = (vm >> r) & 1u;
-            const uint32_t d = zk[r] & 255u;
-            uint64_t m = wave_ballot(valid);
-#pragma unroll
-            for (int b = 0; b < 8; ++b) {
-                const bool bit = (d >> b) & 1u;
-                const uint64_t bb = wave_ballot(bit);
-                m &= bit ? bb : ~bb;
-            }
-            const uint32_t below = rank_below(m);
-            uint32_t prior = 0;
-            if (valid) prior = s_whist[w][d];
-            rk[r] = prior + below;
-            if (valid && below == 0) s_whist[w][d] = prior + (uint32_t)__popcll(m);
-        }
-        __syncthreads();
-        uint32_t dt = 0;   // thread t = digit t: prefix over the waves, then over the digits
-#pragma unroll
-        for (int ww = 0; ww < 4; ++ww) {
-            const uint32_t x = s_whist[ww][t];
-            s_whist[ww][t] = dt;
-            dt += x;
-        }
-        uint32_t ntot;
-        const uint32_t ls = block_excl_scan<uint32_t, 4>(dt, s_wv, ntot);
-        s_lstart[t] = ls;
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < kScanItems; ++r) {
-            if ((vm >> r) & 1u) {
-                const uint32_t d = zk[r] & 255u;
-                const uint32_t pos = s_lstart[d] + s_whist[w][d] + rk[r];
-                s_dk[pos] = zk[r];
-                s_dv[pos] = (uint32_t)(c0 + (int64_t)(w * (64 * kScanItems) + r * 64 + lane));
-            }
-        }
-        __syncthreads();
-        for (uint32_t j = t; j < ntot; j += 256) {
-            const uint32_t z = s_dk[j], d = z & 255u;
-            const uint32_t dst = s_gbase[d] + (j - s_lstart[d]);
-            dkeys[dst] = z;
-            dvals[dst] = s_dv[j];
-        }
     }
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
@@ -378,6 +294,154 @@ __global__ __launch_bounds__(256) void k_scan_down(const uint32_t *__restrict__ 
             dkeys[vbase + j] = s_dk[j];
             dvals[vbase + j] = s_dv[j];
         }
+    }
+}
+
+// Down-sweep that is also the depth sort's first pass (ScanSort): offsets of all counts, and
+// the (depth bits, index) pairs of the Gaussians with keys stably ordered by their low
+// kScanBits depth bits, ranked as k_radix_down ranks. 1,024 threads for a chunk of 4,096:
+// there is about one chunk per CU at 1M Gaussians, so what counts is the length of its chain
+// (loads, scan, ranking rounds, prefixes), and 16 waves take 4 rounds where 4 took 16
+// (18.3 us for 20.1 at 1M, 14.4 for 16.2 at 200k). Wave w holds entries [256 w, 256 w + 256), 64 per round; thread t digit t.
+__global__ __launch_bounds__(1024) void k_scan_sort(const uint32_t *__restrict__ cnt, const uint32_t *__restrict__ zbits,
+                                                    uint32_t *__restrict__ off, int64_t n, const uint64_t *__restrict__ pk,
+                                                    const uint32_t *__restrict__ pv, uint32_t *__restrict__ dkeys,
+                                                    uint32_t *__restrict__ dvals, int fold, ScanFold f,
+                                                    const uint32_t *__restrict__ dcnt, const uint32_t *__restrict__ dtot) {
+    static_assert(kScanDigits == 1024 && kScanChunk == 4096, "a digit and four entries per thread");
+    constexpr int R = 4;
+    __shared__ uint16_t s_whist[16][kScanDigits];   // per-wave digit counts, then per-wave digit prefix
+    __shared__ uint32_t s_gbase[kScanDigits];       // global position of the chunk's first pair of each digit
+    __shared__ uint16_t s_lstart[kScanDigits];      // position in the LDS stage of each digit
+    __shared__ uint32_t s_dk[kScanChunk], s_dv[kScanChunk];
+    __shared__ uint64_t s_k[16];
+    __shared__ uint32_t s_w[16], s_sum[16], s_dsum[16], s_v[16], s_mn[16], s_mx[16];
+    const uint32_t t = threadIdx.x, lane = lane_id(), w = t >> 6;
+    const bool b0 = blockIdx.x == 0;
+    const int64_t c0 = (int64_t)blockIdx.x * kScanChunk + w * 256 + lane;
+    uint32_t c[R], z[R];   // every load of the workgroup goes out here
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int64_t i = min(c0 + 64 * r, n - 1);
+        c[r] = cnt[i];
+        z[r] = zbits[i];
+    }
+    const uint32_t tot = dtot[t], ofs = dcnt[(size_t)t * gridDim.x + blockIdx.x];
+    // fold (up to 1,024 chunks): the key counts of the chunks before this one, a thread
+    // each; workgroup 0 the totals and the depth range, for the header
+    uint64_t fk = 0;
+    uint32_t fv = 0, mn = 0xffffffffu, mx = 0u;
+    if (fold) {
+        if (t < (b0 ? f.nchunks : blockIdx.x)) fk = pk[t];
+        if (b0 && t < f.nchunks) {
+            fv = pv[t];
+            mn = f.pzmn[t];
+            mx = f.pzmx[t];
+        }
+    } else if (t == 0) {   // scanned by k_scan_top
+        fk = pk[blockIdx.x];
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) reinterpret_cast<uint32_t *>(&s_whist[0][0])[t + 1024 * i] = 0u;
+    // offsets (their low 32 bits, as they are kept): prefix within the round, the rounds, the waves
+    uint32_t ex[R], run = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (c0 + 64 * r >= n) c[r] = 0u;
+        const uint32_t inc = wave_incl_scan(c[r]);
+        ex[r] = run + inc - c[r];
+        run += __shfl(inc, 63, 64);
+    }
+    const uint32_t tinc = wave_incl_scan(tot);
+    fk = wave_sum(fk);
+    if (b0 && fold) {
+        fv = wave_sum(fv);
+        mn = wave_min(mn);
+        mx = wave_max(mx);
+    }
+    if (lane == 63) {
+        s_sum[w] = run;
+        s_dsum[w] = tinc;
+        s_k[w] = fk;
+        s_v[w] = fv;
+        s_mn[w] = mn;
+        s_mx[w] = mx;
+    }
+    __syncthreads();
+    uint64_t pre_k = 0;
+    uint32_t dpre = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        pre_k += s_k[k];
+        dpre += k < (int)w ? s_dsum[k] : 0u;
+    }
+    if (b0 && fold) {
+        if (t == 0) {
+            for (int k = 1; k < 16; ++k) { fv += s_v[k]; mn = min(mn, s_mn[k]); mx = max(mx, s_mx[k]); }
+            write_counts(f.header, f.note, pre_k, fv, mn, mx, f.key_capacity);
+        }
+        pre_k = 0;
+    }
+    s_gbase[t] = dpre + tinc - tot + ofs;
+    uint32_t base = (uint32_t)pre_k;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) base += k < (int)w ? s_sum[k] : 0u;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (c0 + 64 * r < n) off[c0 + 64 * r] = base + ex[r];
+    uint32_t rk[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const bool valid = c[r] != 0u;
+        const uint32_t d = z[r] & (kScanDigits - 1u);
+        uint64_t m = wave_ballot(valid);
+#pragma unroll
+        for (int b = 0; b < kScanBits; ++b) {
+            const bool bit = (d >> b) & 1u;
+            const uint64_t bb = wave_ballot(bit);
+            m &= bit ? bb : ~bb;
+        }
+        const uint32_t below = rank_below(m);
+        uint32_t prior = 0;
+        if (valid) prior = s_whist[w][d];
+        rk[r] = prior + below;
+        if (valid && below == 0) s_whist[w][d] = (uint16_t)(prior + (uint32_t)__popcll(m));
+    }
+    __syncthreads();
+    uint32_t dt = 0, ntot;   // thread t = digit t: prefix over the waves, then over the digits
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        const uint32_t x = s_whist[k][t];
+        s_whist[k][t] = (uint16_t)dt;
+        dt += x;
+    }
+    const uint32_t linc = wave_incl_scan(dt);
+    if (lane == 63) s_w[w] = linc;
+    __syncthreads();
+    uint32_t lpre = 0;
+    ntot = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        lpre += k < (int)w ? s_w[k] : 0u;
+        ntot += s_w[k];
+    }
+    s_lstart[t] = (uint16_t)(lpre + linc - dt);
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (c[r]) {
+            const uint32_t d = z[r] & (kScanDigits - 1u);
+            const uint32_t pos = (uint32_t)s_lstart[d] + s_whist[w][d] + rk[r];
+            s_dk[pos] = z[r];
+            s_dv[pos] = (uint32_t)(c0 + 64 * r);
+        }
+    }
+    __syncthreads();
+    for (uint32_t j = t; j < ntot; j += 1024) {
+        const uint32_t k = s_dk[j], d = k & (kScanDigits - 1u);
+        const uint32_t dst = s_gbase[d] + (j - s_lstart[d]);
+        dkeys[dst] = k;
+        dvals[dst] = s_dv[j];
     }
 }
 
@@ -449,8 +513,7 @@ __global__ __launch_bounds__(256) void k_emit(const uint32_t *__restrict__ cnt, 
 // index), emit (tile id, index) pairs; a stable sort on the tile id then yields the
 // (tile, depth, index) order.
 //   k_emit_reduce:  per chunk of 1,024 depth-ordered Gaussians, gathers each one's
-//                   tile rectangle once and sums the chunk's key counts (for one view
-//                   the depth sort's last pass does this as it writes the order)
+//                   tile rectangle once and sums the chunk's key counts
 //   k_scan_top_u32: chunk sums -> chunk key offsets (more than 2,048 chunks)
 //   k_emit_offsets: per-Gaussian key offsets, and for every block of kEmitKeys keys
 //                   the Gaussian owning its first key
@@ -463,18 +526,25 @@ __global__ __launch_bounds__(256) void k_emit(const uint32_t *__restrict__ cnt, 
 // for k_emit_down); every Gaussian in the order has at least one key
 __global__ __launch_bounds__(256) void k_emit_reduce(const uint32_t *__restrict__ order, uint32_t V,
                                                      const uint2 *__restrict__ rect, uint2 *__restrict__ srect,
-                                                     uint32_t *__restrict__ esum, const uint32_t *dynV) {
+                                                     uint32_t *__restrict__ esum, const uint32_t *dynV,
+                                                     const uint32_t *overflow) {
     if (dynV) V = *dynV;
+    if (overflow && *overflow) return;   // V may then exceed srect
     __shared__ uint32_t s_w[4];
     const uint32_t base = blockIdx.x * (uint32_t)kEmitChunk + threadIdx.x;
-    uint32_t sum = 0;
+    if (blockIdx.x * (uint32_t)kEmitChunk >= V) return;
+    uint32_t g[kEmitItems], sum = 0;   // the gathers of a thread go out together, at clamped places
+    uint2 rc[kEmitItems];
+#pragma unroll
+    for (int r = 0; r < kEmitItems; ++r) g[r] = order[min(base + r * 256, V - 1u)];
+#pragma unroll
+    for (int r = 0; r < kEmitItems; ++r) rc[r] = rect[g[r]];
 #pragma unroll
     for (int r = 0; r < kEmitItems; ++r) {
         const uint32_t j = base + r * 256;
         if (j < V) {
-            const uint2 rc = rect[order[j]];
-            srect[j] = rc;
-            sum += rect_count(rc);
+            srect[j] = rc[r];
+            sum += rect_count(rc[r]);
         }
     }
     sum = wave_sum(sum);
@@ -911,7 +981,7 @@ void launch_scan(const uint32_t *cnt, const uint32_t *zbits, uint32_t *off, int6
     if (sort) {
         hipLaunchKernelGGL(k_scan_reduce<true>, dim3(nchunks), dim3(256), 0, st, cnt, zbits, n, pk, pv, pzmn, pzmx,
                            sort->dcnt, nchunks);
-        launch_rowscan(sort->dcnt, nchunks, (uint32_t)kScanChunk, sort->dtot, (uint32_t)n, 8, st);
+        launch_rowscan(sort->dcnt, nchunks, (uint32_t)kScanChunk, sort->dtot, (uint32_t)n, kScanBits, st);
     } else {
         hipLaunchKernelGGL(k_scan_reduce<false>, dim3(nchunks), dim3(256), 0, st, cnt, zbits, n, pk, pv, pzmn, pzmx,
                            nullptr, nchunks);
@@ -926,13 +996,13 @@ void launch_scan(const uint32_t *cnt, const uint32_t *zbits, uint32_t *off, int6
     if (emit) {
         const uint32_t nblk = (uint32_t)(((uint64_t)key_capacity + kEmitKeys - 1) / kEmitKeys);
         hipLaunchKernelGGL(k_scan_down<SD_EMIT>, dim3(nchunks), dim3(256), 0, st, cnt, zbits, off, n, pk, pv, dkeys, dvals,
-                           emit->rect, emit->srect, emit->eoff, emit->efirst, nblk, fold, f, nullptr, nullptr);
+                           emit->rect, emit->srect, emit->eoff, emit->efirst, nblk, fold, f);
     } else if (sort) {
-        hipLaunchKernelGGL(k_scan_down<SD_SORT>, dim3(nchunks), dim3(256), 0, st, cnt, zbits, off, n, pk, pv, sort->keys,
-                           sort->vals, nullptr, nullptr, nullptr, nullptr, 0u, fold, f, sort->dcnt, sort->dtot);
+        hipLaunchKernelGGL(k_scan_sort, dim3(nchunks), dim3(1024), 0, st, cnt, zbits, off, n, pk, pv, sort->keys, sort->vals,
+                           fold, f, sort->dcnt, sort->dtot);
     } else {
         hipLaunchKernelGGL(k_scan_down<SD_COMPACT>, dim3(nchunks), dim3(256), 0, st, cnt, zbits, off, n, pk, pv, dkeys,
-                           dvals, nullptr, nullptr, nullptr, nullptr, 0u, fold, f, nullptr, nullptr);
+                           dvals, nullptr, nullptr, nullptr, nullptr, 0u, fold, f);
     }
 }
 
@@ -951,20 +1021,19 @@ void launch_emit_compacted(const uint32_t *order, uint32_t V, const uint2 *srect
 }
 
 // V is the count or, with dynV, its upper bound; hdr (optional) supplies the overflow flag.
-// folded 2: the offsets are in eoff / efirst already (k_small_order), only the keys are left.
+// ready: srect, eoff and efirst are there already (k_small_order), only the keys are left.
 void launch_emit_sorted(const uint32_t *order, uint32_t V, const uint2 *rect, uint2 *srect, int tiles_x,
                         uint32_t *esum, uint32_t *eoff, uint32_t *efirst, uint32_t K, uint32_t *tkeys, uint32_t *tvals,
                         hipStream_t st, const uint32_t *dynV, const uint32_t *dynK, const uint32_t *hdr,
-                        const uint4 *vtab, int nviews, int folded, const KeyCount *kc) {
+                        const uint4 *vtab, int nviews, bool ready, const KeyCount *kc) {
     if (V == 0 || K == 0) return;
     const uint32_t chunks = (V + kEmitChunk - 1) / kEmitChunk;
     const uint32_t nblk = (K + kEmitKeys - 1) / kEmitKeys;
     const uint32_t *ovf = hdr ? hdr + H_OVERFLOW : nullptr;
-    // folded: the depth sort's last pass has gathered srect and summed esum (EmitFold)
-    if (!folded) hipLaunchKernelGGL(k_emit_reduce, dim3(chunks), dim3(256), 0, st, order, V, rect, srect, esum, dynV);
     // up to 2,048 chunks (2M depth-ordered Gaussians) the offsets pass scans the sums itself
     const int fold = chunks <= 2048u;
-    if (folded < 2) {
+    if (!ready) {
+        hipLaunchKernelGGL(k_emit_reduce, dim3(chunks), dim3(256), 0, st, order, V, rect, srect, esum, dynV, ovf);
         if (!fold) hipLaunchKernelGGL(k_scan_top_u32, dim3(1), dim3(1024), 0, st, esum, chunks);
         hipLaunchKernelGGL(k_emit_offsets, dim3(chunks), dim3(256), 0, st, srect, V, esum, eoff, efirst, nblk, dynV, ovf,
                            fold);

@@ -284,17 +284,40 @@ struct ScanEmit {
 };
 
 // The count scan as the first pass of the depth sort (one view, no host read-back): the
-// scan's chunks are that pass's chunks. k_scan_reduce counts the low 8 bits of the depth
-// bits of each chunk's Gaussians with keys into dcnt[digit][chunk] (row stride: the
+// scan's chunks are that pass's chunks. k_scan_reduce counts the low kScanBits bits of the
+// depth bits of each chunk's Gaussians with keys into dcnt[digit][chunk] (row stride: the
 // chunk count), a row scan makes them the chunks' digit offsets and dtot the digit
 // totals, and k_scan_down writes the chunk's (depth bits, index) pairs stably ordered
-// by those 8 bits (keys, vals) instead of compacted in index order.
+// by those bits (keys, vals) instead of compacted in index order.
+// 10 bits: the rest is at most 22 bits of (depth bits >> 10) - (smallest >> 10), and 16 for
+// depths within a factor of 256 (8 octaves of 2^23 values), so two further passes order
+// any scene and take 8-bit digits in nearly every one (DepthDigits).
+constexpr int kScanBits = 10;
+constexpr uint32_t kScanDigits = 1u << kScanBits;
 struct ScanSort {
     uint32_t *dcnt;
     uint32_t *dtot;
     uint32_t *keys;
     uint32_t *vals;
 };
+
+// Digits of the two passes that follow, from the depth range that the scan left in the
+// header: bits [0, nb1) and [nb1, nb1 + nb2) of (depth bits >> kScanBits) - base. A pass of
+// no bits is a stable copy.
+constexpr int kDepthBitsMax = 11;
+struct DepthDigits {
+    uint32_t base;
+    int nb1, nb2;
+};
+__host__ __device__ inline DepthDigits depth_digits(uint32_t zmin, uint32_t zmax) {
+    DepthDigits d;
+    d.base = zmin >> kScanBits;
+    int bits = 0;
+    for (uint32_t r = (zmax >> kScanBits) - d.base; r; r >>= 1) ++bits;
+    d.nb1 = bits <= 8 ? bits : (bits + 1) / 2;
+    d.nb2 = bits - d.nb1;
+    return d;
+}
 
 // The first pass of the key sort counted by the key emission: block b of the emission
 // (its keys [2048 b, 2048 b + 2048)) is chunk b of that pass, whose digit counts (the
@@ -319,17 +342,6 @@ constexpr int kEmitChunk = 256 * kEmitItems;         // depth-ordered Gaussians 
 __device__ __forceinline__ uint32_t rect_count(uint2 r) {
     return ((r.x >> 16) - (r.x & 0xffffu) + 1u) * ((r.y >> 16) - (r.y & 0xffffu) + 1u);
 }
-
-// Work of the key emission's reduce pass, done by the last pass of the depth sort as it
-// writes the depth order: each Gaussian's tile rectangle gathered in that order (srect)
-// and the key count of every kEmitChunk consecutive depth-ordered Gaussians added into
-// esum (zeroed beforehand).
-struct EmitFold {
-    const uint2 *rect;   // tile rectangles, indexed by the sort's values
-    uint2 *srect;        // srect_cap entries (positions past it are not written)
-    uint32_t *esum;
-    uint32_t srect_cap;
-};
 
 // Per-Gaussian splat record for compositing: three float4
 //   r0 = (u, v, ex, ey)   centre (pixels) and half-extents of the alpha >= 1/255 box

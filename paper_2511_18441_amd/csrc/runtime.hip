@@ -34,7 +34,7 @@ void launch_tile_depth_sort(const uint2 *, uint32_t, uint32_t *, const uint32_t 
                             hipStream_t);
 void launch_emit_sorted(const uint32_t *, uint32_t, const uint2 *, uint2 *, int, uint32_t *, uint32_t *, uint32_t *,
                         uint32_t, uint32_t *, uint32_t *, hipStream_t, const uint32_t *, const uint32_t *,
-                        const uint32_t *, const uint4 *, int, int = 0, const KeyCount * = nullptr);
+                        const uint32_t *, const uint4 *, int, bool = false, const KeyCount * = nullptr);
 uint32_t emit_blocks(uint32_t K);
 size_t sort_count_words(uint64_t K_max);
 void launch_ranges(const uint64_t *, uint32_t, uint2 *, hipStream_t);
@@ -45,7 +45,10 @@ int sort_passes(int total_bits);
 int radix_sort_tile_depth64(uint64_t *, uint32_t *, uint64_t *, uint32_t *, uint32_t, uint32_t, int, int, uint32_t *,
                             uint32_t *, hipStream_t);
 int radix_sort_u32(uint32_t *, uint32_t *, uint32_t *, uint32_t *, uint32_t, uint32_t, int, uint32_t *, uint32_t *,
-                   hipStream_t, const EmitFold * = nullptr, bool = false);
+                   hipStream_t, bool = false);
+void launch_depth_pass(const uint32_t *, const uint32_t *, uint32_t *, uint32_t *, uint32_t, bool, const uint32_t *, uint32_t *,
+                       uint32_t *, hipStream_t);
+size_t depth_count_words(uint64_t);
 bool launch_blend_bwd(int, int, int, int, const uint2 *, const uint32_t *, const SplatRec *, const uint2 *, const uint32_t *,
                       int, int, int, const float *, const float *, const uint32_t *, float4 *, const uint32_t *, hipStream_t);
 bool launch_bwd_prep(float4 *, const uint32_t *, int64_t, const uint2 *, uint32_t, uint32_t *, hipStream_t);
@@ -72,8 +75,7 @@ size_t outlier_workspace_bytes(int64_t);
 bool launch_outliers(const float *, int64_t, int64_t, int, float, float *, uint8_t *, float *, int64_t, uint32_t *, void *,
                      hipStream_t);
 int radix_sort_u32_dyn(uint32_t *, uint32_t *, uint32_t *, uint32_t *, uint32_t, const uint32_t *, const uint32_t *, int,
-                       uint32_t *, uint32_t *, hipStream_t, const EmitFold * = nullptr, int = 0, bool = false,
-                       bool = false);
+                       uint32_t *, uint32_t *, hipStream_t, bool = false, bool = false);
 KeyCount key_sort_first_count(uint32_t *, uint32_t, int);
 void launch_preprocess_batch(int, int, uint32_t, const ViewDev *, int, SplatRec *, uint32_t *, uint2 *, uint32_t *,
                              hipStream_t);
@@ -145,18 +147,20 @@ size_t layout(recogs_workspace *ws, int64_t n, int32_t W, int32_t H, int32_t tw,
     // scan partials per chunk: key count (u64), count with keys, depth min, depth max
     ws->off_scan = take(20 * (size_t)scan_chunks);
     ws->off_efirst = take(4 * ((size_t)emit_blocks((uint32_t)(cap > 0 ? cap : 1)) + 1));
-    // radix digit-count matrix [256][chunks], shared by the depth sort (up to n keys) and
-    // the key sort (up to cap keys)
-    ws->off_sort_count = take(4 * std::max(sort_count_words((uint64_t)nn), sort_count_words((uint64_t)(cap > 0 ? cap : 1))));
+    // radix digit-count matrix, shared by the depth sort ([2048][chunks], up to n keys) and
+    // the key sort ([256][chunks], up to cap keys)
+    const size_t count_words = std::max(depth_count_words((uint64_t)nn), sort_count_words((uint64_t)(cap > 0 ? cap : 1)));
+    ws->off_sort_count = take(4 * count_words);
+    // digit totals of the scan's pass and of the depth sort's two
+    ws->off_dhist = take(4 * (kScanDigits + 2 * (1u << kDepthBitsMax)));
     // zeroed each render: header; histograms; key counts of the depth-ordered emission
     // chunks (summed by the depth sort's last pass); tile ranges
     ws->off_header = take(4 * H_WORDS);
     ws->off_hist = take(4 * 256 * kMaxPasses);
-    ws->off_dhist = take(4 * 256 * kMaxPasses);
     ws->off_esum = take(4 * (size_t)((nn + kEmitChunk - 1) / kEmitChunk));
     ws->off_ranges = take(8 * (size_t)T);
     ws->scan_chunks = (size_t)scan_chunks;
-    ws->sort_chunks = std::max(sort_count_words((uint64_t)nn), sort_count_words((uint64_t)(cap > 0 ? cap : 1))) / 256;
+    ws->sort_chunks = count_words / 256;
     ws->tiles_x = (int32_t)tiles_x;
     ws->tiles_y = (int32_t)tiles_y;
     return o;
@@ -445,7 +449,7 @@ static recogs_status render_async(const recogs_scene *scene, const recogs_camera
     ws->depth_min_bits = 0;
     ws->key_bits = tbits + 32;
     ws->sort_passes = sort_passes(tbits);
-    ws->depth_passes = mode == 0 ? sort_passes(24) : 0;   // after the scan's pass
+    ws->depth_passes = mode == 0 ? 2 : 0;   // after the scan's pass
     ws->key_bytes = 4;
     int alt = 0;
     if (n > 0 && cap > 0) {
@@ -456,30 +460,29 @@ static recogs_status render_async(const recogs_scene *scene, const recogs_camera
             if ((s = tm.mark(4)) != RECOGS_OK) return s;
             launch_emit_sorted(dv0, (uint32_t)n, at<uint2>(ws, ws->off_rect), (uint2 *)t1, cd.tiles_x, nullptr, dv1,
                                at<uint32_t>(ws, ws->off_efirst), cap, t0, v0, stream, hdr + H_V, hdr + H_KEFF, hdr, nullptr,
-                               1, 2, &kc);
+                               1, true, &kc);
         } else if (mode == 0) {
             // the depth order's rectangles go to keys1, free until the key sort (cap entries;
             // past them the view overflows and emits nothing)
             uint2 *srect = (uint2 *)t1;
-            const EmitFold ef{at<uint2>(ws, ws->off_rect), srect, at<uint32_t>(ws, ws->off_esum), cap};
-            // the scan left the pairs ordered by their low 8 depth bits in dkeys1 (digit
-            // totals in dhist[0..255]); three passes over the upper 24 bits remain
-            // (the passes load their chunks below n before the live count V arrives: at worst
-            // the n - V pairs past it are read for nothing)
-            const int dalt = radix_sort_u32_dyn(dk1, dv1, dk0, dv0, (uint32_t)n, hdr + H_V, nullptr, 24, dhist + 256,
-                                                scount, stream, &ef, 8, false, true);
-            uint32_t *order = dalt ? dv0 : dv1, *spare = dalt ? dv1 : dv0;
+            // the scan left the pairs ordered by their low depth bits in dkeys1; two passes
+            // over the rest remain (they load their chunks below n before the live count V
+            // arrives: at worst the n - V pairs past it are read for nothing)
+            launch_depth_pass(dk1, dv1, dk0, dv0, (uint32_t)n, false, hdr, dhist + kScanDigits, scount, stream);
+            launch_depth_pass(dk0, dv0, dk1, dv1, (uint32_t)n, true, hdr, dhist + kScanDigits + (1u << kDepthBitsMax), scount,
+                              stream);
+            uint32_t *order = dv1, *spare = dv0;
             if ((s = tm.mark(4)) != RECOGS_OK) return s;
             launch_emit_sorted(order, (uint32_t)n, at<uint2>(ws, ws->off_rect), srect, cd.tiles_x,
                                at<uint32_t>(ws, ws->off_esum), spare, at<uint32_t>(ws, ws->off_efirst), cap, t0, v0, stream,
-                               hdr + H_V, hdr + H_KEFF, hdr, nullptr, 1, 1, &kc);
+                               hdr + H_V, hdr + H_KEFF, hdr, nullptr, 1, false, &kc);
         } else {
             if ((s = tm.mark(4)) != RECOGS_OK) return s;
             launch_emit_compacted(dv0, (uint32_t)n, (const uint2 *)dk0, dv1, at<uint32_t>(ws, ws->off_efirst), cap,
                                   cd.tiles_x, t0, v0, stream, hdr + H_V, hdr + H_KEFF, hdr, nullptr, 1, &kc);
         }
         if ((s = tm.mark(5)) != RECOGS_OK) return s;
-        alt = radix_sort_u32_dyn(t0, v0, t1, v1, cap, hdr + H_KEFF, nullptr, tbits, hist, scount, stream, nullptr, 0, true);
+        alt = radix_sort_u32_dyn(t0, v0, t1, v1, cap, hdr + H_KEFF, nullptr, tbits, hist, scount, stream, true);
         if ((s = tm.mark(6)) != RECOGS_OK) return s;
         launch_ranges32(alt ? t1 : t0, cap, ranges, stream, hdr + H_KEFF);
         if ((s = tm.mark(7)) != RECOGS_OK) return s;
@@ -665,7 +668,7 @@ recogs_status recogs_render(const recogs_scene *scene, const recogs_camera *cam,
         // tile-first order: the compaction carries rectangles (over both depth-key buffers,
         // adjacent), key offsets (dvals1) and the emission blocks' owners
         const ScanEmit em{rect, (uint2 *)dk0, dv1, at<uint32_t>(ws, ws->off_efirst)};
-        // depth-first order: the scan also does the depth sort's first pass, on the low 8
+        // depth-first order: the scan also does the depth sort's first pass, on the low
         // raw depth bits (the minimum is not known yet; raw bits give the same order), into
         // dkeys1
         const ScanSort so{at<uint32_t>(ws, ws->off_sort_count), at<uint32_t>(ws, ws->off_dhist), dk1, dv1};
@@ -677,8 +680,8 @@ recogs_status recogs_render(const recogs_scene *scene, const recogs_camera *cam,
     if (opts->graph_mode) return render_async(scene, cam, opts, ws, image, stream, cd, tm);
 
     // The counts decide the rest's grids and passes. They come through the note; in sort
-    // mode 0 the depth sort's next pass (bits 8-15, nearly always needed; a stable copy when
-    // the depths agree in them) is enqueued first, so the GPU has work while the counts travel
+    // mode 0 the depth sort's next pass (nearly always needed; a stable copy when the depths
+    // differ in the scan's bits only) is enqueued first, so the GPU has work while the counts travel
     // and the rest is enqueued. Against a copy of the header and a wait for it: a frame of
     // 4,096 Gaussians at 128 x 128 171 -> 135 us, one of 200k at 800 x 800 226 -> 185 us.
     uint32_t h[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -687,8 +690,7 @@ recogs_status recogs_render(const recogs_scene *scene, const recogs_camera *cam,
     if (note.words) {
         if ((s = tm.mark(3)) != RECOGS_OK) return s;
         if (mode == 0 && !small) {
-            radix_sort_u32_dyn(dk1, dv1, dk0, dv0, (uint32_t)n, hdr + H_V, nullptr, 8, dhist + 256, scount, stream, nullptr,
-                               8, false, true);
+            launch_depth_pass(dk1, dv1, dk0, dv0, (uint32_t)n, false, hdr, dhist + kScanDigits, scount, stream);
             early = true;
             if ((s = hip_check("depth sort")) != RECOGS_OK) return s;
         }
@@ -719,11 +721,9 @@ recogs_status recogs_render(const recogs_scene *scene, const recogs_camera *cam,
     ws->depth_min_bits = zmin;
     ws->key_bits = tbits + dbits;
     ws->sort_passes = K ? sort_passes(key_bits) : 0;
-    // sort mode 0: raw depth bits up to the highest one in which the depths differ; the
-    // scan sorted bits 0-7, the depth sort takes the rest
-    const int rbits = K ? bits_for((uint64_t)(zmin ^ zmax)) : 0;
-    const int rest_bits = rbits > 8 ? rbits - 8 : 0;
-    ws->depth_passes = (mode == 0 && V) ? sort_passes(rest_bits) : 0;
+    // sort mode 0: the passes that the range of the depth bits above the scan's needs
+    const DepthDigits dd = depth_digits(K ? zmin : 0u, K ? zmax : 0u);
+    ws->depth_passes = (mode == 0 && V) ? (dd.nb1 > 0) + (dd.nb2 > 0) : 0;
     ws->key_bytes = mode == 1 ? 8 : 4;
 
     // (histograms, emission sums and tile ranges zeroed by the preprocess launch)
@@ -737,35 +737,33 @@ recogs_status recogs_render(const recogs_scene *scene, const recogs_camera *cam,
         if ((s = tm.mark(4)) != RECOGS_OK) return s;
         const KeyCount kc = key_sort_first_count(scount, (uint32_t)K, key_bits);
         launch_emit_sorted(dv0, V, rect, (uint2 *)k1, cd.tiles_x, nullptr, dv1, at<uint32_t>(ws, ws->off_efirst), (uint32_t)K,
-                           t0, v0, stream, nullptr, nullptr, nullptr, nullptr, 1, 2, &kc);
+                           t0, v0, stream, nullptr, nullptr, nullptr, nullptr, 1, true, &kc);
         if ((s = tm.mark(5)) != RECOGS_OK) return s;
-        alt = radix_sort_u32(t0, v0, t1, v1, (uint32_t)K, 0u, key_bits, hist, scount, stream, nullptr, true);
+        alt = radix_sort_u32(t0, v0, t1, v1, (uint32_t)K, 0u, key_bits, hist, scount, stream, true);
         if ((s = tm.mark(6)) != RECOGS_OK) return s;
         launch_ranges32(alt ? t1 : t0, (uint32_t)K, ranges, stream, nullptr);
         if ((s = tm.mark(7)) != RECOGS_OK) return s;
     } else if (K > 0 && mode == 0) {
         // the rest of the depth sort of the V Gaussians with keys (the scan left them ordered
-        // by their low 8 depth bits in dkeys1); its last pass gathers the depth-ordered
+        // by their low depth bits in dkeys1); the emission gathers the depth-ordered
         // rectangles (8 bytes each) into keys1, free until the key sort (K <= cap, so
-        // V <= cap), and sums the emission chunks' counts
+        // V <= cap)
         uint32_t *t0 = (uint32_t *)k0, *t1 = (uint32_t *)k1;
         uint2 *srect = (uint2 *)k1;
-        const EmitFold ef{rect, srect, at<uint32_t>(ws, ws->off_esum), (uint32_t)ws->key_capacity};
-        const int done = early ? 8 : 0;   // of the rest's bits
-        const int left = rest_bits > done ? rest_bits - done : 0;
-        uint32_t *ka = early ? dk0 : dk1, *va = early ? dv0 : dv1, *kb = early ? dk1 : dk0, *vb = early ? dv1 : dv0;
-        const int dalt = radix_sort_u32_dyn(ka, va, kb, vb, V, nullptr, nullptr, left, dhist + (early ? 512 : 256), scount,
-                                            stream, &ef, 8 + done);
-        uint32_t *order = dalt ? vb : va, *spare = dalt ? va : vb;
+        if (!early)
+            launch_depth_pass(dk1, dv1, dk0, dv0, V, false, hdr, dhist + kScanDigits, scount, stream);
+        const bool two = dd.nb2 > 0;
+        if (two)
+            launch_depth_pass(dk0, dv0, dk1, dv1, V, true, hdr, dhist + kScanDigits + (1u << kDepthBitsMax), scount, stream);
+        uint32_t *order = two ? dv1 : dv0, *spare = two ? dv0 : dv1;
         if ((s = tm.mark(4)) != RECOGS_OK) return s;
-        // per-Gaussian key offsets go to the depth-value buffer the sort left free; with no
-        // pass left (depths equal above the bits sorted by then) the emission does its own reduce
+        // per-Gaussian key offsets go to the depth-value buffer the sort left free
         const KeyCount kc = key_sort_first_count(scount, (uint32_t)K, key_bits);
         launch_emit_sorted(order, V, rect, srect, cd.tiles_x, at<uint32_t>(ws, ws->off_esum), spare,
                            at<uint32_t>(ws, ws->off_efirst), (uint32_t)K, t0, v0, stream, nullptr, nullptr, nullptr,
-                           nullptr, 1, left > 0 ? 1 : 0, &kc);
+                           nullptr, 1, false, &kc);
         if ((s = tm.mark(5)) != RECOGS_OK) return s;
-        alt = radix_sort_u32(t0, v0, t1, v1, (uint32_t)K, 0u, key_bits, hist, scount, stream, nullptr, true);
+        alt = radix_sort_u32(t0, v0, t1, v1, (uint32_t)K, 0u, key_bits, hist, scount, stream, true);
         if ((s = tm.mark(6)) != RECOGS_OK) return s;
         launch_ranges32(alt ? t1 : t0, (uint32_t)K, ranges, stream, nullptr);
         if ((s = tm.mark(7)) != RECOGS_OK) return s;
@@ -778,7 +776,7 @@ recogs_status recogs_render(const recogs_scene *scene, const recogs_camera *cam,
         launch_emit_compacted(dv0, V, (const uint2 *)dk0, dv1, at<uint32_t>(ws, ws->off_efirst), (uint32_t)K, cd.tiles_x,
                               t0, v0, stream, nullptr, nullptr, nullptr, nullptr, 1, &kc);
         if ((s = tm.mark(5)) != RECOGS_OK) return s;
-        alt = radix_sort_u32(t0, v0, t1, v1, (uint32_t)K, 0u, key_bits, hist, scount, stream, nullptr, true);
+        alt = radix_sort_u32(t0, v0, t1, v1, (uint32_t)K, 0u, key_bits, hist, scount, stream, true);
         if ((s = tm.mark(6)) != RECOGS_OK) return s;
         launch_ranges32(alt ? t1 : t0, (uint32_t)K, ranges, stream, nullptr);
         if ((s = tm.mark(7)) != RECOGS_OK) return s;
