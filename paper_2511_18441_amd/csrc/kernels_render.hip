@@ -749,7 +749,7 @@ __device__ __forceinline__ uint32_t block_excl_max256(uint32_t v, uint32_t *s_w)
     return pre;
 }
 
-// Batches (nviews > 1): values are (view, Gaussian) pair indices and tile ids are global,
+// Batches (vtab): values are (view, Gaussian) pair indices and tile ids are global,
 // tile_base(view) + local id; vtab[v] = (pair_base, tile_base, tiles_x, -) per view.
 __global__ __launch_bounds__(256) void k_emit_down(const uint32_t *__restrict__ order, uint32_t V, uint32_t K,
                                                    const uint2 *__restrict__ srect, const uint32_t *__restrict__ eoff,
@@ -786,7 +786,7 @@ __global__ __launch_bounds__(256) void k_emit_down(const uint32_t *__restrict__ 
         const bool in = gi < V && st < k1;
         if (in) {
             uint32_t tb = 0, txn = (uint32_t)tiles_x;
-            if (nviews > 1) {  // view of the pair: last v with pair_base <= gv
+            if (vtab) {  // view of the pair: last v with pair_base <= gv
                 int lo = 0, hi = nviews - 1;
                 while (lo < hi) {
                     const int mid = (lo + hi + 1) >> 1;
