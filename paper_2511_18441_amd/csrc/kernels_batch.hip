@@ -33,13 +33,19 @@ __device__ __forceinline__ int view_of_tile(const ViewDev *views, int nviews, ui
     return lo;
 }
 
+// Bound by memory: a Gaussian's scene values are read once per view of its scene. The blocks of
+// a run of views of one scene alternate, eight chunks of 256 Gaussians of one view, the
+// same eight of the next, ..: the blocks of one chunk follow one another on one XCD, so all
+// but the first find the chunk in its L2 (8 scenes from 4 cameras each, 37M pairs: 1453 ->
+// 1176 us).
 template <int DT, int DEG>
 __global__ __launch_bounds__(256) void k_preprocess_batch(const ViewDev *__restrict__ views, int nviews,
                                                           SplatRec *__restrict__ rec, uint32_t *__restrict__ zbits,
                                                           uint2 *__restrict__ rect, uint32_t *__restrict__ count) {
-    const int v = view_of_block(views, nviews, blockIdx.x);
-    const ViewDev &vw = views[v];
-    const int64_t i = (int64_t)(blockIdx.x - vw.blk_base) * 256 + threadIdx.x;
+    const ViewDev &rv = views[view_of_block(views, nviews, blockIdx.x)];   // a view of the block's run
+    const uint32_t local = blockIdx.x - rv.blk_base, r = local % (8u * rv.run_len);
+    const ViewDev &vw = views[rv.run_first + r / 8u];
+    const int64_t i = (int64_t)(local / (8u * rv.run_len) * 8u + r % 8u) * 256 + threadIdx.x;
     if (i < vw.sc.n)
         preprocess_one<DT, DEG>(vw.sc, vw.cam, vw.rc, 0, i, (int64_t)vw.pair_base + i, rec, nullptr, zbits, rect, count);
 }

@@ -317,8 +317,9 @@ __global__ __launch_bounds__(1024) void k_scan_sort(const uint32_t *__restrict__
     __shared__ uint64_t s_k[16];
     __shared__ uint32_t s_w[16], s_sum[16], s_dsum[16], s_v[16], s_mn[16], s_mx[16];
     const uint32_t t = threadIdx.x, lane = lane_id(), w = t >> 6;
-    const bool b0 = blockIdx.x == 0;
-    const int64_t c0 = (int64_t)blockIdx.x * kScanChunk + w * 256 + lane;
+    const uint32_t chunk = xcd_chunk<3, 5>(blockIdx.x, gridDim.x);
+    const bool b0 = chunk == 0;
+    const int64_t c0 = (int64_t)chunk * kScanChunk + w * 256 + lane;
     uint32_t c[R], z[R];   // every load of the workgroup goes out here
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -326,20 +327,20 @@ __global__ __launch_bounds__(1024) void k_scan_sort(const uint32_t *__restrict__
         c[r] = cnt[i];
         z[r] = zbits[i];
     }
-    const uint32_t tot = dtot[t], ofs = dcnt[(size_t)t * gridDim.x + blockIdx.x];
+    const uint32_t tot = dtot[t], ofs = dcnt[(size_t)t * gridDim.x + chunk];
     // fold (up to 1,024 chunks): the key counts of the chunks before this one, a thread
     // each; workgroup 0 the totals and the depth range, for the header
     uint64_t fk = 0;
     uint32_t fv = 0, mn = 0xffffffffu, mx = 0u;
     if (fold) {
-        if (t < (b0 ? f.nchunks : blockIdx.x)) fk = pk[t];
+        if (t < (b0 ? f.nchunks : chunk)) fk = pk[t];
         if (b0 && t < f.nchunks) {
             fv = pv[t];
             mn = f.pzmn[t];
             mx = f.pzmx[t];
         }
     } else if (t == 0) {   // scanned by k_scan_top
-        fk = pk[blockIdx.x];
+        fk = pk[chunk];
     }
 #pragma unroll
     for (int i = 0; i < 8; ++i) reinterpret_cast<uint32_t *>(&s_whist[0][0])[t + 1024 * i] = 0u;

@@ -131,7 +131,7 @@ __global__ __launch_bounds__(256) void k_radix_down(const KT *__restrict__ kin, 
                                                     const uint32_t *dyn_zmin, int spec) {
     constexpr uint32_t CHUNK = 256 * ITEMS;
     const uint32_t t = threadIdx.x, lane = lane_id(), w = t >> 6;
-    const uint32_t chunk = blockIdx.x;
+    const uint32_t chunk = xcd_chunk<0, 3>(blockIdx.x, gridDim.x);
     const uint32_t cbase = chunk * (uint32_t)CHUNK;
     // every global load of the workgroup goes out first (the chunk's keys and values, the
     // digit totals, this chunk's digit offsets): one memory round trip, not three; with
@@ -387,7 +387,7 @@ __global__ __launch_bounds__(256) void k_depth_down(const uint32_t *__restrict__
     __shared__ uint32_t s_w[4];
     __shared__ uint32_t s_keys[CHUNK], s_vals[CHUNK];
     const uint32_t t = threadIdx.x, lane = lane_id(), w = t >> 6;
-    const uint32_t chunk = blockIdx.x, cbase = chunk * CHUNK;
+    const uint32_t chunk = xcd_chunk<2, 4>(blockIdx.x, gridDim.x), cbase = chunk * CHUNK;
     uint32_t key[ITEMS], val[ITEMS], rank[ITEMS];   // loaded below the bound, before the header is in
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {

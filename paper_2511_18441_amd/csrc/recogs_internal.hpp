@@ -273,7 +273,10 @@ struct ViewDev {
     float *image;
     float bg[3];
     uint32_t pair_base, blk_base, tile_base, ntiles;
+    uint32_t run_first, run_len;   // consecutive views of one scene (blk_base is the run's)
 };
+// preprocess blocks of one view of n Gaussians in its run: whole groups of eight
+inline uint32_t preprocess_blocks_padded(int64_t n) { return (uint32_t)((n + 2047) / 2048 * 8); }
 
 // Outputs of the count scan's compaction for the tile-first key order (see launch_scan).
 struct ScanEmit {
@@ -300,6 +303,21 @@ struct ScanSort {
     uint32_t *keys;
     uint32_t *vals;
 };
+
+// Chunk of workgroup b in a pass that scatters: workgroups go to the 8 XCDs in turn, and G
+// consecutive chunks go to one XCD, whose L2 then joins the short runs they write side by
+// side into whole lines (a line written from several XCDs leaves each as a partial write).
+// G = 2^SMALL, or 2^LARGE from 2,048 chunks on: with few chunks a large G leaves XCDs idle at
+// the end, with many the writes bound the pass. 28M pairs, G = 1 against these: k_scan_sort 584
+// -> 482 us, k_depth_down 226 + 208 -> 199 + 195, k_radix_down (56M keys) 637 + 397 -> 538 + 333;
+// 0.7M pairs: k_scan_sort 18.3 -> 15.9 (G = 8; 18.5 with 32), k_depth_down 12.3 + 8.6 -> 10.5 +
+// 9.7 (4), k_radix_down 18.3 + 16.1 (1; 18.4 + 16.9 with 4). The last grid % (8 G) workgroups
+// keep their place.
+template <int SMALL, int LARGE> __device__ __forceinline__ uint32_t xcd_chunk(uint32_t b, uint32_t grid) {
+    const uint32_t lg = grid >= 2048u ? LARGE : SMALL, q = b >> (lg + 3u);
+    if (q >= grid >> (lg + 3u)) return b;
+    return (q << (lg + 3u)) + ((b & 7u) << lg) + ((b >> 3) & ((1u << lg) - 1u));
+}
 
 // Digits of the two passes that follow, from the depth range that the scan left in the
 // header: bits [0, nb1) and [nb1, nb1 + nb2) of (depth bits >> kScanBits) - base. A pass of

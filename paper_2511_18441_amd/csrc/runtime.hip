@@ -1138,7 +1138,8 @@ size_t batch_layout(recogs_batch_workspace *ws, const recogs_batch_view *views, 
     ws->off_scan = take(20 * (size_t)scan_chunks);
     ws->off_esum = take(4 * (size_t)((pp + kEmitChunk - 1) / kEmitChunk));
     ws->off_efirst = take(4 * ((size_t)emit_blocks((uint32_t)cc) + 1));
-    ws->off_sort_count = take(4 * std::max(sort_count_words((uint64_t)pp), sort_count_words((uint64_t)cc)));
+    ws->off_sort_count = take(4 * std::max(depth_count_words((uint64_t)pp), sort_count_words((uint64_t)cc)));
+    ws->off_dhist = take(4 * (kScanDigits + 2 * (1u << kDepthBitsMax)));
     ws->off_keys0 = take(4 * (size_t)cc);
     ws->off_keys1 = take(4 * (size_t)cc);
     ws->off_vals0 = take(4 * (size_t)cc);
@@ -1147,7 +1148,6 @@ size_t batch_layout(recogs_batch_workspace *ws, const recogs_batch_view *views, 
     // zeroed each batch (contiguous): header, histograms, tile ranges
     ws->off_header = take(4 * H_WORDS);
     ws->off_hist = take(4 * 256 * kMaxPasses);
-    ws->off_dhist = take(4 * 256 * kMaxPasses);
     ws->off_ranges = take(8 * (size_t)(T > 0 ? T : 1));
     ws->scan_chunks = (size_t)scan_chunks;
     ws->pairs = P;
@@ -1213,13 +1213,22 @@ recogs_status recogs_batch_init(recogs_batch_workspace *ws, void *dev_mem, size_
         vd[v].image = bv.image;
         for (int c = 0; c < 3; ++c) vd[v].bg[c] = opts->bg[c];
         vd[v].pair_base = pair;
-        vd[v].blk_base = blk;
+        // consecutive views of one scene form a run, whose blocks alternate between its views
+        const bool same = v > 0 && memcmp(&vd[v].sc, &vd[v - 1].sc, sizeof(SceneDev)) == 0;
+        vd[v].run_first = same ? vd[v - 1].run_first : (uint32_t)v;
         vd[v].tile_base = tile;
         vd[v].ntiles = (uint32_t)(vd[v].cam.tiles_x * vd[v].cam.tiles_y);
         vt[v] = make_uint4(pair, tile, (uint32_t)vd[v].cam.tiles_x, 0u);
         pair += (uint32_t)bv.scene.n;
-        blk += (uint32_t)((bv.scene.n + 255) / 256);
         tile += vd[v].ntiles;
+    }
+    for (int v = 0, e; v < nviews; v = e) {
+        for (e = v; e < nviews && vd[e].run_first == (uint32_t)v; ++e) {
+            vd[e].blk_base = blk;
+            vd[e].run_len = 0;
+        }
+        for (int k = v; k < e; ++k) vd[k].run_len = (uint32_t)(e - v);
+        blk += (uint32_t)(e - v) * preprocess_blocks_padded(vd[v].sc.n);
     }
     ws->preprocess_blocks = blk;
     hipError_t e1 = hipMemcpy((char *)dev_mem + ws->off_views, vd, sizeof(ViewDev) * (size_t)nviews, hipMemcpyHostToDevice);
@@ -1255,14 +1264,17 @@ recogs_status recogs_render_batch(const recogs_batch_workspace *ws, hipStream_t 
         const size_t sc_n = ws->scan_chunks;
         uint64_t *pk = (uint64_t *)B(ws->off_scan);
         uint32_t *pv = (uint32_t *)(pk + sc_n);
-        launch_scan(cnt, zb, off, P, pk, pv, pv + sc_n, pv + 2 * sc_n, dk0, dv0, hdr, ws->key_capacity, stream, nullptr);
+        // also the first pass of the depth sort of the pairs with keys, into dkeys1
+        const ScanSort so{scount, dhist, dk1, dv1};
+        launch_scan(cnt, zb, off, P, pk, pv, pv + sc_n, pv + 2 * sc_n, dk0, dv0, hdr, ws->key_capacity, stream, nullptr, &so);
     }
-    // depth sort of the pairs with keys over all 32 depth bits above the minimum
-    const int dalt = radix_sort_u32_dyn(dk0, dv0, dk1, dv1, P, hdr + H_V, hdr + H_ZMIN_RAW, 32, dhist, scount, stream);
-    launch_emit_sorted(dalt ? dv1 : dv0, P, rect, (uint2 *)dk0, 0, (uint32_t *)B(ws->off_esum), dalt ? dv0 : dv1,
-                       (uint32_t *)B(ws->off_efirst), cap, k0, v0, stream, hdr + H_V, hdr + H_KEFF, hdr,
-                       (const uint4 *)B(ws->off_vtab), ws->nviews);
-    const int alt = radix_sort_u32_dyn(k0, v0, k1, v1, cap, hdr + H_KEFF, nullptr, ws->tile_bits, hist, scount, stream);
+    launch_depth_pass(dk1, dv1, dk0, dv0, P, false, hdr, dhist + kScanDigits, scount, stream);
+    launch_depth_pass(dk0, dv0, dk1, dv1, P, true, hdr, dhist + kScanDigits + (1u << kDepthBitsMax), scount, stream);
+    const KeyCount kc = key_sort_first_count(scount, cap, ws->tile_bits);
+    launch_emit_sorted(dv1, P, rect, (uint2 *)dk0, 0, (uint32_t *)B(ws->off_esum), dv0, (uint32_t *)B(ws->off_efirst), cap, k0,
+                       v0, stream, hdr + H_V, hdr + H_KEFF, hdr, (const uint4 *)B(ws->off_vtab), ws->nviews, false, &kc);
+    const int alt =
+        radix_sort_u32_dyn(k0, v0, k1, v1, cap, hdr + H_KEFF, nullptr, ws->tile_bits, hist, scount, stream, true);
     launch_ranges32(alt ? k1 : k0, cap, ranges, stream, hdr + H_KEFF);
     launch_tile_order(ranges, T, hdr + H_ORDER_HIST, hdr + H_ORDER_CUR, (uint32_t *)B(ws->off_order), stream);
     if (!launch_blend_persistent(ws->tile_w, ws->tile_h, ws->px_per_thread, (uint32_t)ws->persistent_blocks, views,

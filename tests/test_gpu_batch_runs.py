@@ -1,5 +1,5 @@
-"""Batches give
-the images of single renders, bit for bit, for one view, for runs of
+"""Batches deal the preprocess blocks of consecutive views of one scene in turn, and take their
+depth order in three passes: the images and lists of single renders, bit for bit, for runs of
 one to three views, a scene that comes back later, ragged and empty scenes."""
 import numpy as np
 import pytest
