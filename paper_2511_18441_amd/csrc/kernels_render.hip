@@ -351,7 +351,7 @@ __global__ __launch_bounds__(1024) void k_scan_sort(const uint32_t *__restrict__
         if (c0 + 64 * r >= n) c[r] = 0u;
         const uint32_t inc = wave_incl_scan(c[r]);
         ex[r] = run + inc - c[r];
-        run += __shfl(inc, 63, 64);
+        run += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
     }
     const uint32_t tinc = wave_incl_scan(tot);
     fk = wave_sum(fk);
@@ -395,13 +395,7 @@ __global__ __launch_bounds__(1024) void k_scan_sort(const uint32_t *__restrict__
     for (int r = 0; r < R; ++r) {
         const bool valid = c[r] != 0u;
         const uint32_t d = z[r] & (kScanDigits - 1u);
-        uint64_t m = wave_ballot(valid);
-#pragma unroll
-        for (int b = 0; b < kScanBits; ++b) {
-            const bool bit = (d >> b) & 1u;
-            const uint64_t bb = wave_ballot(bit);
-            m &= bit ? bb : ~bb;
-        }
+        const uint64_t m = wave_match(valid, d, kScanBits);
         const uint32_t below = rank_below(m);
         uint32_t prior = 0;
         if (valid) prior = s_whist[w][d];
@@ -486,7 +480,7 @@ __global__ __launch_bounds__(256) void k_emit(const uint32_t *__restrict__ cnt, 
         if (c) { r = rect[g]; zb = zbits[g]; }
     }
     const uint32_t inc = wave_incl_scan(c);
-    const uint32_t total = __shfl(inc, 63, 64);
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
     const uint32_t base = __shfl(o, 0, 64);
     s_ex[w][lane] = inc - c;
     s_rect[w][lane] = r;
@@ -733,12 +727,7 @@ void launch_small_order(const uint32_t *cnt, const uint32_t *zbits, const uint2 
 // exclusive max-scan over the workgroup of one value per thread (256 threads; 0 for thread 0)
 __device__ __forceinline__ uint32_t block_excl_max256(uint32_t v, uint32_t *s_w) {
     const uint32_t lane = lane_id(), w = threadIdx.x >> 6;
-    uint32_t inc = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t x = __shfl_up(inc, o, 64);
-        if (lane >= (uint32_t)o) inc = x > inc ? x : inc;
-    }
+    const uint32_t inc = wave_incl_max(v);
     if (lane == 63) s_w[w] = inc;
     __syncthreads();
     uint32_t pre = __shfl_up(inc, 1, 64);

@@ -174,12 +174,7 @@ __global__ __launch_bounds__(256) void k_radix_down(const KT *__restrict__ kin, 
         const uint32_t idx = cbase + w * (64 * ITEMS) + r * 64 + lane;
         const bool valid = idx < K;
         const uint32_t d = digit_of<KT, VIEW>(key[r], zmin, dbits, shift, dmask);
-        uint64_t m = wave_ballot(valid);
-        for (int b = 0; b < nbits; ++b) {
-            const bool bit = (d >> b) & 1u;
-            const uint64_t bb = wave_ballot(bit);
-            m &= bit ? bb : ~bb;
-        }
+        const uint64_t m = wave_match(valid, d, nbits);
         const uint32_t below = rank_below(m);
         uint32_t prior = 0;
         if (valid) prior = s_whist[w][d];
@@ -425,12 +420,7 @@ __global__ __launch_bounds__(256) void k_depth_down(const uint32_t *__restrict__
         const uint32_t idx = cbase + w * (64 * ITEMS) + r * 64 + lane;
         const bool valid = idx < a.V;
         const uint32_t d = depth_digit(key[r], a, dmask);
-        uint64_t m = wave_ballot(valid);
-        for (int b = 0; b < a.nb; ++b) {
-            const bool bit = (d >> b) & 1u;
-            const uint64_t bb = wave_ballot(bit);
-            m &= bit ? bb : ~bb;
-        }
+        const uint64_t m = wave_match(valid, d, a.nb);
         const uint32_t below = rank_below(m);
         uint32_t prior = 0;
         if (valid) prior = s_whist[w][d];

@@ -81,12 +81,7 @@ __device__ __forceinline__ void ts_rank(const uint32_t (&key)[IT], uint32_t (&po
         if (r >= R) continue;   // uniform: the loop stays fully unrolled
         const bool valid = ts_idx(R, r) < len;
         const uint32_t d = (key[r] >> shift) & dmask;
-        uint64_t m = wave_ballot(valid);
-        for (int b = 0; b < nb; ++b) {
-            const bool bit = (d >> b) & 1u;
-            const uint64_t bb = wave_ballot(bit);
-            m &= bit ? bb : ~bb;
-        }
+        const uint64_t m = wave_match(valid, d, nb);
         const uint32_t below = rank_below(m);
         uint32_t prior = 0;
         if (valid) prior = sh.wh[w][d];
