@@ -88,10 +88,10 @@ __global__ __launch_bounds__(256) void k_scan_reduce(const uint32_t *__restrict_
             if constexpr (HIST) atomicAdd(&s_h[z & (kScanDigits - 1u)], 1u);
         }
     }
-    tsum = wave_sum(tsum);
-    vsum = wave_sum(vsum);
-    zmn = wave_min(zmn);
-    zmx = wave_max(zmx);
+    tsum = wave_total(tsum);
+    vsum = wave_total(vsum);
+    zmn = wave_least(zmn);
+    zmx = wave_most(zmx);
     if (lane == 0) { s_k[w] = tsum; s_v[w] = vsum; s_zmn[w] = zmn; s_zmx[w] = zmx; }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -130,8 +130,8 @@ __global__ __launch_bounds__(1024) void k_scan_top(uint64_t *__restrict__ pk, ui
         runk += ktot;
         runv += vtot;
     }
-    zmn = wave_min(zmn);
-    zmx = wave_max(zmx);
+    zmn = wave_least(zmn);
+    zmx = wave_most(zmx);
     if (lane == 0) { s_zmn[w] = zmn; s_zmx[w] = zmx; }
     __syncthreads();
     if (t == 0) {
@@ -173,9 +173,9 @@ __device__ __forceinline__ void scan_fold_prefix(const uint64_t *__restrict__ pk
         v += pv[c];
         if (blockIdx.x == 0) { mn = min(mn, f.pzmn[c]); mx = max(mx, f.pzmx[c]); }
     }
-    k = wave_sum(k);
-    v = wave_sum(v);
-    if (blockIdx.x == 0) { mn = wave_min(mn); mx = wave_max(mx); }
+    k = wave_total(k);
+    v = wave_total(v);
+    if (blockIdx.x == 0) { mn = wave_least(mn); mx = wave_most(mx); }
     if (lane_id() == 0) { s_k[w] = k; s_v[w] = v; s_mn[w] = mn; s_mx[w] = mx; }
     __syncthreads();
     k = ((s_k[0] + s_k[1]) + s_k[2]) + s_k[3];
@@ -354,11 +354,11 @@ __global__ __launch_bounds__(1024) void k_scan_sort(const uint32_t *__restrict__
         run += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
     }
     const uint32_t tinc = wave_incl_scan(tot);
-    fk = wave_sum(fk);
+    fk = wave_total(fk);
     if (b0 && fold) {
-        fv = wave_sum(fv);
-        mn = wave_min(mn);
-        mx = wave_max(mx);
+        fv = wave_total(fv);
+        mn = wave_least(mn);
+        mx = wave_most(mx);
     }
     if (lane == 63) {
         s_sum[w] = run;
@@ -542,7 +542,7 @@ __global__ __launch_bounds__(256) void k_emit_reduce(const uint32_t *__restrict_
             sum += rect_count(rc[r]);
         }
     }
-    sum = wave_sum(sum);
+    sum = wave_total(sum);
     if (lane_id() == 0) s_w[threadIdx.x >> 6] = sum;
     __syncthreads();
     if (threadIdx.x == 0) esum[blockIdx.x] = s_w[0] + s_w[1] + s_w[2] + s_w[3];
@@ -571,7 +571,7 @@ __global__ __launch_bounds__(256) void k_emit_offsets(const uint2 *__restrict__ 
     if (fold) {
         uint32_t a = 0;
         for (uint32_t c = t; c < blockIdx.x; c += 256) a += epre[c];
-        a = wave_sum(a);
+        a = wave_total(a);
         if (lane_id() == 0) s_w[t >> 6] = a;
         __syncthreads();
         pre = ((s_w[0] + s_w[1]) + s_w[2]) + s_w[3];
@@ -647,12 +647,12 @@ __global__ __launch_bounds__(1024) void k_small_order(const uint32_t *__restrict
         pre += j < i0 ? c[r] : 0u;
         zc[j] = make_uint2(z[r], c[r]);
     }
-    ksum = wave_sum(ksum);
-    pre = wave_sum(pre);
+    ksum = wave_total(ksum);
+    pre = wave_total(pre);
     if (blockIdx.x == 0) {
-        vsum = wave_sum(vsum);
-        mn = wave_min(mn);
-        mx = wave_max(mx);
+        vsum = wave_total(vsum);
+        mn = wave_least(mn);
+        mx = wave_most(mx);
     }
     if (lane == 0) { s_k[w] = ksum; s_pre[w] = pre; s_v[w] = vsum; s_mn[w] = mn; s_mx[w] = mx; }
     __syncthreads();

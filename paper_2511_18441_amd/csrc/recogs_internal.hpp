@@ -207,10 +207,11 @@ template <typename T> __device__ __forceinline__ T wave_incl_scan(T v) {
     return v;
 }
 
-// 32-bit (the block scans and the sort passes are chains of these: with wave_match, 3 to 6% of
+// 32-bit: by DPP moves (shifts within the 16-lane rows, then the rows' last lanes broadcast
+// into the rows behind them), six vector instructions and no LDS crossbar. All 64 lanes active.
+// The block scans and the sort passes are chains of these: with wave_match 3 to 6% of
 // k_depth_down / k_radix_down at 1M and 10% at 200k, k_scan_sort 16.2 -> 15.0 and 14.8 -> 13.1
-// us, and 473 -> 298 over a batch's 37M pairs): by DPP moves (shifts within the 16-lane rows, then the rows' last lanes broadcast into
-// the rows behind them), six vector instructions and no LDS crossbar. All 64 lanes active.
+// us, and 473 -> 298 over a batch's 37M pairs.
 template <int CTRL, int ROWS> __device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
 }
@@ -223,6 +224,24 @@ template <> __device__ __forceinline__ uint32_t wave_incl_scan<uint32_t>(uint32_
     v += dpp_or_zero<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
     return v;
 }
+// totals by the same moves (in every lane); the minimum through the complements' maximum.
+// k_scan_reduce 7.2 -> 6.6 us at 1M and 4.8 -> 4.3 at 200k, k_small_order 7.5 -> 6.9 at 4,096.
+__device__ __forceinline__ uint32_t wave_total(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(v), 63);
+}
+template <int CTRL, int ROWS> __device__ __forceinline__ uint64_t dpp_or_zero64(uint64_t v) {
+    return ((uint64_t)dpp_or_zero<CTRL, ROWS>((uint32_t)(v >> 32)) << 32) | dpp_or_zero<CTRL, ROWS>((uint32_t)v);
+}
+__device__ __forceinline__ uint64_t wave_total(uint64_t v) {
+    v += dpp_or_zero64<0x111, 0xf>(v);
+    v += dpp_or_zero64<0x112, 0xf>(v);
+    v += dpp_or_zero64<0x114, 0xf>(v);
+    v += dpp_or_zero64<0x118, 0xf>(v);
+    v += dpp_or_zero64<0x142, 0xa>(v);
+    v += dpp_or_zero64<0x143, 0xc>(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 63);
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), 63) << 32) | lo;
+}
 // the same with the maximum
 __device__ __forceinline__ uint32_t wave_incl_max(uint32_t v) {
     v = max(v, dpp_or_zero<0x111, 0xf>(v));
@@ -233,6 +252,10 @@ __device__ __forceinline__ uint32_t wave_incl_max(uint32_t v) {
     v = max(v, dpp_or_zero<0x143, 0xc>(v));
     return v;
 }
+__device__ __forceinline__ uint32_t wave_most(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_max(v), 63);
+}
+__device__ __forceinline__ uint32_t wave_least(uint32_t v) { return ~wave_most(~v); }
 
 // ---------------------------------------------------------------------------
 // Device-side views of the host structs
