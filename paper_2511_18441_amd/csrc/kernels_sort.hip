@@ -49,30 +49,19 @@ __device__ __forceinline__ uint32_t block_excl_scan256(uint32_t v, uint32_t *s_w
     return pre + inc - v;
 }
 
-// Counts and the depth minimum may live in device memory (dyn_count, dyn_zmin non-null:
-// the graph-capturable batch, whose host code never reads them back); grids are then
-// sized for the capacity and workgroups past the live count return at once.
-__device__ __forceinline__ void dyn_args(const uint32_t *dyn_count, const uint32_t *dyn_zmin, uint32_t &K, uint32_t &zmin) {
-    if (dyn_count) K = *dyn_count;
-    if (dyn_zmin) zmin = *dyn_zmin;
-}
+// The count may live in device memory (dyn_count non-null: the graph-capturable renders,
+// whose host code never reads it back); grids are then sized for the capacity and
+// workgroups past the live count return at once.
 
 // per-chunk digit counts -> cnt[digit * chunks + chunk]; a chunk is 256 x ITEMS keys.
-// spec (a device count whose bound K is near it): the chunk's keys are loaded below the
-// bound before the count arrives, so the count costs no round trip of its own
 template <typename KT, int VIEW, int ITEMS>
 __global__ __launch_bounds__(256) void k_radix_up(const KT *__restrict__ kin, uint32_t K, uint32_t zmin, int dbits,
                                                   int shift, int nbits, uint32_t *__restrict__ cnt, uint32_t chunks,
-                                                  const uint32_t *dyn_count, const uint32_t *dyn_zmin, int spec) {
+                                                  const uint32_t *dyn_count) {
     constexpr uint32_t CHUNK = 256 * ITEMS;
     const uint32_t t = threadIdx.x;
     const uint32_t base = blockIdx.x * CHUNK;
-    KT kk[ITEMS];
-    if (spec) {
-#pragma unroll
-        for (int r = 0; r < ITEMS; ++r) kk[r] = base + r * 256 + t < K ? kin[base + r * 256 + t] : (KT)0;
-    }
-    dyn_args(dyn_count, dyn_zmin, K, zmin);
+    if (dyn_count) K = *dyn_count;
     if (base >= K) return;
     __shared__ uint32_t h[256];
     h[t] = 0;
@@ -81,7 +70,7 @@ __global__ __launch_bounds__(256) void k_radix_up(const KT *__restrict__ kin, ui
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
         const uint32_t idx = base + r * 256 + t;
-        if (idx < K) atomicAdd(&h[digit_of<KT, VIEW>(spec ? kk[r] : kin[idx], zmin, dbits, shift, dmask)], 1u);
+        if (idx < K) atomicAdd(&h[digit_of<KT, VIEW>(kin[idx], zmin, dbits, shift, dmask)], 1u);
     }
     __syncthreads();
     if (t <= dmask) cnt[(size_t)t * chunks + blockIdx.x] = h[t];
@@ -127,30 +116,24 @@ __global__ __launch_bounds__(256) void k_radix_down(const KT *__restrict__ kin, 
                                                     KT *__restrict__ kout, uint32_t *__restrict__ vout, uint32_t K,
                                                     uint32_t zmin, int dbits, int shift, int nbits,
                                                     const uint32_t *__restrict__ off, const uint32_t *__restrict__ dtot,
-                                                    uint32_t chunks, const uint32_t *dyn_count,
-                                                    const uint32_t *dyn_zmin, int spec) {
+                                                    uint32_t chunks, const uint32_t *dyn_count) {
     constexpr uint32_t CHUNK = 256 * ITEMS;
     const uint32_t t = threadIdx.x, lane = lane_id(), w = t >> 6;
     const uint32_t chunk = xcd_chunk<0, 3>(blockIdx.x, gridDim.x);
     const uint32_t cbase = chunk * (uint32_t)CHUNK;
     // every global load of the workgroup goes out first (the chunk's keys and values, the
-    // digit totals, this chunk's digit offsets): one memory round trip, not three; with
-    // spec (as k_radix_up) the keys and values go out before a device count too
+    // digit totals, this chunk's digit offsets): one memory round trip, not three
     KT key[ITEMS];
     uint32_t val[ITEMS], rank[ITEMS];
-    auto load_items = [&]() {
-#pragma unroll
-        for (int r = 0; r < ITEMS; ++r) {
-            const uint32_t idx = cbase + w * (64 * ITEMS) + r * 64 + lane;
-            const bool valid = idx < K;
-            key[r] = valid ? kin[idx] : (KT)0;
-            val[r] = valid ? vin[idx] : 0u;
-        }
-    };
-    if (spec) load_items();
-    dyn_args(dyn_count, dyn_zmin, K, zmin);
+    if (dyn_count) K = *dyn_count;
     if (cbase >= K) return;
-    if (!spec) load_items();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const uint32_t idx = cbase + w * (64 * ITEMS) + r * 64 + lane;
+        const bool valid = idx < K;
+        key[r] = valid ? kin[idx] : (KT)0;
+        val[r] = valid ? vin[idx] : 0u;
+    }
     __shared__ uint32_t s_whist[4][256];   // per-wave digit counts, then per-wave digit prefix
     __shared__ uint32_t s_gbase[256];      // global position of this chunk's first key of each digit
     __shared__ uint32_t s_lstart[256];     // position in the LDS stage of each digit
@@ -248,7 +231,7 @@ KeyCount key_sort_first_count(uint32_t *cnt, uint32_t K_max, int total_bits) {
 template <typename KT, int VIEW>
 static int radix_sort(KT *ka, uint32_t *va, KT *kb, uint32_t *vb, uint32_t K, uint32_t zmin, int dbits, int total_bits,
                       uint32_t *ghist, uint32_t *cnt, hipStream_t st, const uint32_t *dyn_count = nullptr,
-                      const uint32_t *dyn_zmin = nullptr, bool first_counted = false, bool spec = false) {
+                      bool first_counted = false) {
     if (K == 0 || total_bits == 0) return 0;   // K is the count, or its upper bound with dyn_count
     const int passes = sort_passes(total_bits);
     const int per = (total_bits + passes - 1) / passes;
@@ -274,10 +257,10 @@ static int radix_sort(KT *ka, uint32_t *va, KT *kb, uint32_t *vb, uint32_t K, ui
 #define RECOGS_PASS(IT)                                                                                                    \
     if (p > 0 || !first_counted)                                                                                           \
         hipLaunchKernelGGL((k_radix_up<KT, VIEW, IT>), dim3(chunks), dim3(256), 0, st, kin, K, zmin, dbits, shift, nb,     \
-                           cnt, chunks, dyn_count, dyn_zmin, (int)spec);                                                   \
+                           cnt, chunks, dyn_count);                                                                        \
     hipLaunchKernelGGL(k_radix_rowscan, dim3(1u << nb), dim3(256), 0, st, cnt, chunks, chunk_keys, tot, K, dyn_count);     \
     hipLaunchKernelGGL((k_radix_down<KT, VIEW, IT>), dim3(chunks), dim3(256), 0, st, kin, vin, kout, vout, K, zmin, dbits, \
-                       shift, nb, cnt, tot, chunks, dyn_count, dyn_zmin, (int)spec);
+                       shift, nb, cnt, tot, chunks, dyn_count);
         if (items == 16) { RECOGS_PASS(16) }
         else if (items == 8) { RECOGS_PASS(8) }
         else { RECOGS_PASS(4) }
@@ -510,17 +493,14 @@ int radix_sort_tile_depth64(uint64_t *ka, uint32_t *va, uint64_t *kb, uint32_t *
 // first_counted: the key emission wrote the first pass's counts (key_sort_first_count).
 int radix_sort_u32(uint32_t *ka, uint32_t *va, uint32_t *kb, uint32_t *vb, uint32_t K, uint32_t sub, int total_bits,
                    uint32_t *ghist, uint32_t *cnt, hipStream_t st, bool first_counted) {
-    return radix_sort<uint32_t, KV_SUB>(ka, va, kb, vb, K, sub, 0, total_bits, ghist, cnt, st, nullptr, nullptr, first_counted);
+    return radix_sort<uint32_t, KV_SUB>(ka, va, kb, vb, K, sub, 0, total_bits, ghist, cnt, st, nullptr, first_counted);
 }
 
-// The same with the count and the subtracted minimum read from device memory; K_max
-// bounds the count (sizes the grids and the count matrix). spec: the count is expected near K_max (the workgroups past it then load their chunk for
-// nothing), and the chunks are loaded before it arrives.
+// The same with the count read from device memory; K_max bounds it (sizes the grids and the
+// count matrix).
 int radix_sort_u32_dyn(uint32_t *ka, uint32_t *va, uint32_t *kb, uint32_t *vb, uint32_t K_max, const uint32_t *dyn_count,
-                       const uint32_t *dyn_sub, int total_bits, uint32_t *ghist, uint32_t *cnt, hipStream_t st,
-                       bool first_counted, bool spec) {
-    return radix_sort<uint32_t, KV_SUB>(ka, va, kb, vb, K_max, 0u, 0, total_bits, ghist, cnt, st, dyn_count, dyn_sub,
-                                        first_counted, spec);
+                       int total_bits, uint32_t *ghist, uint32_t *cnt, hipStream_t st, bool first_counted) {
+    return radix_sort<uint32_t, KV_SUB>(ka, va, kb, vb, K_max, 0u, 0, total_bits, ghist, cnt, st, dyn_count, first_counted);
 }
 
 }  // namespace recogs

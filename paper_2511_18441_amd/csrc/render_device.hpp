@@ -203,15 +203,10 @@ __device__ __forceinline__ void store_pixel(float *__restrict__ image, int64_t p
 
 // One splat record applied to the PPT pixels of a thread (eq. 3, front to back).
 // `idx` is the record's 1-based position in its tile list (kept, with STATE, as the
-// count up to the last blended entry). With DEPTH, cross[j] takes the position of the
-// blended splat that takes the pixel's transmittance from >= tau to < tau (the rough
-// depth of Sec. 3.2; at most one splat per pixel does, as T only decreases). Two
-// compares and a select; a per-pixel flag in a lane mask instead of the compare of T
-// measured slower (its mask updates put scalar instructions between the vector ones).
-template <int PPT, bool STATE, bool DEPTH = false>
+// count up to the last blended entry).
+template <int PPT, bool STATE>
 __device__ __forceinline__ void blend_step(const BlendRec &b, float pxc, const float *pyc, float *T, float *C0, float *C1,
-                                           float *C2, uint32_t *last, uint32_t idx, uint32_t *cross = nullptr,
-                                           float tau = 0.f) {
+                                           float *C2, uint32_t *last, uint32_t idx) {
 #pragma clang fp contract(off)
     const float2 uv = b.uv;
     const float4 r1 = b.r1, r2 = b.rgb;
@@ -231,7 +226,6 @@ __device__ __forceinline__ void blend_step(const BlendRec &b, float pxc, const f
         C1[j] = __builtin_fmaf(r2.y, wgt, C1[j]);
         C2[j] = __builtin_fmaf(r2.z, wgt, C2[j]);
         if constexpr (STATE) last[j] = bl ? idx : last[j];
-        if constexpr (DEPTH) cross[j] = (bl && Tn < tau && T[j] >= tau) ? idx : cross[j];
         const float Ts = stop ? -fabsf(T[j]) : Tn;   // two selects: this form compiles to v_cndmask
         T[j] = ok ? Ts : T[j];
     }
@@ -386,6 +380,9 @@ __device__ __forceinline__ void ring_put(BlendRing &sm, uint32_t slot, const flo
 // 128 us; at 1280 x 720 with STATE 96.6 -> 84.5 us; where waves are few and the chain's latency
 // counts (4,096 Gaussians at 128 x 128), 44.6 -> 31.4 us. The colours by 4x4x1 matrix
 // products instead of the twelve FMAs (the same bits) took 147 us.
+// With DEPTH, cross[j] takes the position of the blended splat that takes the pixel's
+// transmittance from >= tau to < tau (the rough depth of Sec. 3.2; at most one splat per
+// pixel does, as T only decreases).
 template <int PPT, bool STATE, bool DEPTH>
 __device__ __forceinline__ void blend_group(const BlendGroup &g, const float (*pyg)[4], float pxg, float *T, float *Tf,
                                             uint64_t *live, float *C0, float *C1, float *C2, uint32_t *last,

@@ -74,8 +74,8 @@ void launch_tint(const float *, const uint8_t *, const float *, float *, int64_t
 size_t outlier_workspace_bytes(int64_t);
 bool launch_outliers(const float *, int64_t, int64_t, int, float, float *, uint8_t *, float *, int64_t, uint32_t *, void *,
                      hipStream_t);
-int radix_sort_u32_dyn(uint32_t *, uint32_t *, uint32_t *, uint32_t *, uint32_t, const uint32_t *, const uint32_t *, int,
-                       uint32_t *, uint32_t *, hipStream_t, bool = false, bool = false);
+int radix_sort_u32_dyn(uint32_t *, uint32_t *, uint32_t *, uint32_t *, uint32_t, const uint32_t *, int, uint32_t *, uint32_t *,
+                       hipStream_t, bool);
 KeyCount key_sort_first_count(uint32_t *, uint32_t, int);
 void launch_preprocess_batch(int, int, uint32_t, const ViewDev *, int, SplatRec *, uint32_t *, uint2 *, uint32_t *,
                              hipStream_t);
@@ -482,7 +482,7 @@ static recogs_status render_async(const recogs_scene *scene, const recogs_camera
                                   cd.tiles_x, t0, v0, stream, hdr + H_V, hdr + H_KEFF, hdr, nullptr, 1, &kc);
         }
         if ((s = tm.mark(5)) != RECOGS_OK) return s;
-        alt = radix_sort_u32_dyn(t0, v0, t1, v1, cap, hdr + H_KEFF, nullptr, tbits, hist, scount, stream, true);
+        alt = radix_sort_u32_dyn(t0, v0, t1, v1, cap, hdr + H_KEFF, tbits, hist, scount, stream, true);
         if ((s = tm.mark(6)) != RECOGS_OK) return s;
         launch_ranges32(alt ? t1 : t0, cap, ranges, stream, hdr + H_KEFF);
         if ((s = tm.mark(7)) != RECOGS_OK) return s;
@@ -1274,7 +1274,7 @@ recogs_status recogs_render_batch(const recogs_batch_workspace *ws, hipStream_t 
     launch_emit_sorted(dv1, P, rect, (uint2 *)dk0, 0, (uint32_t *)B(ws->off_esum), dv0, (uint32_t *)B(ws->off_efirst), cap, k0,
                        v0, stream, hdr + H_V, hdr + H_KEFF, hdr, (const uint4 *)B(ws->off_vtab), ws->nviews, false, &kc);
     const int alt =
-        radix_sort_u32_dyn(k0, v0, k1, v1, cap, hdr + H_KEFF, nullptr, ws->tile_bits, hist, scount, stream, true);
+        radix_sort_u32_dyn(k0, v0, k1, v1, cap, hdr + H_KEFF, ws->tile_bits, hist, scount, stream, true);
     launch_ranges32(alt ? k1 : k0, cap, ranges, stream, hdr + H_KEFF);
     launch_tile_order(ranges, T, hdr + H_ORDER_HIST, hdr + H_ORDER_CUR, (uint32_t *)B(ws->off_order), stream);
     if (!launch_blend_persistent(ws->tile_w, ws->tile_h, ws->px_per_thread, (uint32_t)ws->persistent_blocks, views,
