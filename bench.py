@@ -829,15 +829,14 @@ def main():
         sq = recorded_sq(kname, tile, args.ppt) if args.storage == "f32" else None
         if sq and "executed_evals_max" in sq:
             # the evaluations the region waves actually execute (64 pixels per wave step,
-            # wave steps bounded by the LDS instruction count), from the committed counters
+            # wave steps bounded by the transcendental count), from the committed counters
             ex = sq["executed_evals_max"]
             roof["executed_evals_max"] = ex
             roof["achieved_executed_max"] = round(ex * BLEND_FLOPS_PER_EVAL / (avg * 1e-3) / 1e12, 3)
             roof["valu_insts_per_launch"] = sq.get("sq_insts_valu")
             if "lds_load_bytes" in sq:
-                # the second limit of the blend: bytes the LDS returns to the lanes (every
-                # wave step broadcasts its 36-byte record to 64 lanes), against 128 bytes per
-                # CU per clock at the 2.4 GHz peak clock
+                # bytes the LDS returns to the lanes (a record's geometry to 16 lanes, its
+                # colour to 64), against 128 bytes per CU per clock at the 2.4 GHz peak clock
                 lds = sq["lds_load_bytes"] / (avg * 1e-3)
                 roof["lds_load_bytes_per_launch"] = sq["lds_load_bytes"]
                 roof["lds_TBps"] = round(lds / 1e12, 2)
