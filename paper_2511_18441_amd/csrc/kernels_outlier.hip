@@ -136,13 +136,17 @@ __global__ __launch_bounds__(256) void k_ol_bbox(const float *__restrict__ pts, 
 }
 
 // 1b. per-axis histograms over the box (LDS counts, then one atomic per bin and
-// workgroup; integer counts, so the result is independent of the order), of every step-th
-// point: they only place the cell size, which no result depends on, and neighbouring
+// workgroup; integer counts, so the result is independent of the order), of one point in
+// every step: they only place the cell size, which no result depends on, and neighbouring
 // points fall into the same bins, whose LDS atomics then wait for each other (15 us over
-// all points of a 314k cloud). Every workgroup reduces the partial boxes for itself (wave w the bounds w and w + 4); workgroup 0 stores
-// the box and clears the queues' counts.
+// all points of a 314k cloud). The point within the step follows the golden ratio's
+// multiples, so that an order with a period (interleaved scans, points dealt in turn) does
+// not show only one of its phases: with always the first, a cloud of 131,072 points dealt
+// in turn to one small and three large clusters took cells a hundred times too small.
+// Every workgroup reduces the partial boxes for itself (wave w the bounds w and w + 4);
+// workgroup 0 stores the box and clears the queues' counts.
 __global__ __launch_bounds__(256) void k_ol_hist(const float *__restrict__ pts, int64_t n, int64_t stride,
-                                                 int64_t step, const float *__restrict__ part, int nblk,
+                                                 int64_t ns, uint32_t step, const float *__restrict__ part, int nblk,
                                                  OlHdr *__restrict__ hdr, uint32_t *__restrict__ hist) {
     __shared__ uint32_t s_h[3 * kOlBins];
     __shared__ float s_box[6];
@@ -169,9 +173,10 @@ __global__ __launch_bounds__(256) void k_ol_hist(const float *__restrict__ pts, 
         const float e = s_box[3 + a] - mn[a];
         sc[a] = e > 0.f ? (float)kOlBins / e : 0.f;
     }
-    for (int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * step; i < n; i += (int64_t)gridDim.x * 256 * step) {
+    for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < ns; q += (int64_t)gridDim.x * 256) {
+        const uint32_t phase = __umulhi((uint32_t)q * 0x9e3779b9u, step);   // 0 .. step - 1
         float p[3];
-        ol_load(pts, stride, i, p[0], p[1], p[2]);
+        ol_load(pts, stride, min(q * step + phase, n - 1), p[0], p[1], p[2]);
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             int b = (int)((p[a] - mn[a]) * sc[a]);
@@ -769,7 +774,8 @@ bool launch_outliers(const float *pts, int64_t n, int64_t stride, int k, float s
     float *bpart = (float *)(b + L.bpart);
     hipLaunchKernelGGL(k_ol_bbox, dim3(rb), dim3(256), 0, st, pts, n, stride, bpart, shist);
     const int64_t step = (n + kOlSample - 1) / kOlSample, ns = (n + step - 1) / step;
-    hipLaunchKernelGGL(k_ol_hist, dim3((unsigned)((ns + 255) / 256)), dim3(256), 0, st, pts, n, stride, step, bpart, rb, hdr, shist);
+    hipLaunchKernelGGL(k_ol_hist, dim3((unsigned)((ns + 255) / 256)), dim3(256), 0, st, pts, n, stride, ns, (uint32_t)step, bpart, rb, hdr,
+                       shist);
     hipLaunchKernelGGL(k_ol_setup, dim3(1), dim3(192), 0, st, shist, ns, n, (uint32_t)bits, hdr);
     hipLaunchKernelGGL(k_ol_key, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, pts, n, stride, hdr, k0, v0);
     const int alt = radix_sort_u32(k0, v0, k1, v1, (uint32_t)n, 0u, bits, (uint32_t *)(b + L.hist),
