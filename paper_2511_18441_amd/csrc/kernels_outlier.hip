@@ -18,9 +18,10 @@
 //      a row of cells along x being one run of points; the search ends once the k-th
 //      distance is within (r - 1/16) h, the distance below which no unscanned cell lies
 //      (the 1/16 absorbs float32 rounding of the cell coordinates). A query has 2, 16 and
-//      64 lanes in the three searches, which merge their lists of the k smallest. Queries
-//      that even the largest cube leaves open (far stray points) go to a search of the
-//      whole cloud by the bounding boxes of its runs of 64 points.
+//      64 lanes in the three searches (4 and 16 of the last two where many queries are
+//      left, and then the largest cube in shells), which merge their lists of the k
+//      smallest. Queries that even the largest cube leaves open (far stray points) go to a
+//      search of the whole cloud by the bounding boxes of its runs of 64 points.
 //      314k points (a brush selection): 285 us for the four, against 980 with one thread
 //      per query over the 27 cells one by one, one wave per query with a cell per lane for
 //      the rest, and a scan of the whole cloud for each stray point.
@@ -39,7 +40,10 @@ void launch_excl_scan_u32(uint32_t *, uint32_t, uint32_t *, hipStream_t);
 constexpr int kOlBins = 1024;
 constexpr int kOlMaxDim = 128;
 constexpr int kOlRing1 = 1, kOlRing2 = 2, kOlRing3 = 5;   // cube radii of the three searches
+constexpr int kOlShell0 = 3;                   // first cube of the third in shells
 constexpr int kOlR1 = 1, kOlC1 = 2, kOlR2 = 4, kOlC2 = 4, kOlR3 = 16, kOlC3 = 4;   // their lanes per query: rows x candidates
+constexpr int kOlR2Many = 2, kOlC2Many = 2, kOlR3Many = 8, kOlC3Many = 2;          // with long lists
+constexpr uint32_t kOlMany2 = 16384, kOlMany3 = 32768;
 constexpr int kOlListBlocks = 2048;            // grid of the second and third (grid-stride over their lists)
 static_assert(2 * kOlRing3 + 1 <= 16, "one search's cells must fit in 16 slot residues per axis");
 constexpr int kOlLeaf = 64;                    // points per bounding box of the whole-cloud search
@@ -377,20 +381,30 @@ template <int K> __device__ __forceinline__ float ol_mean(const float (&best)[K]
 // More lanes per query fill the GPU and balance the rows, fewer leave less to merge:
 // measured at 314k points, (GR, GC) of the radius-1 search (1, 1) 135, (1, 2) 119, (1, 4) 137,
 // (1, 8) 193 us; of the radius-2 search (4, 2) 91, (8, 2) 76, (4, 4) 68; of the radius-5
-// search (16, 2) 75, (8, 8) 49, (16, 4) 42. The queries are all points in slot order (list null) or the listed slot positions, *nlist of
-// them, grid-stride. A query not settled goes to the list `slow` (or, with slow null, to
-// the whole-cloud search, as does any beyond the coordinate guard).
+// search (16, 2) 75, (8, 8) 49, (16, 4) 42. The queries are all points in slot order (list
+// null) or the listed slot positions, `total` of them, grid-stride. A query not settled
+// goes to the list `slow` (or, with slow null, to the whole-cloud search, as does any
+// beyond the coordinate guard).
+struct OlSearch {
+    const float4 *__restrict__ spts;
+    int64_t n;
+    OlHdr *hdr;
+    const uint32_t *__restrict__ start;
+    uint32_t *__restrict__ defer;
+    float *__restrict__ dmean;
+};
 template <int K, int RING, int GR, int GC>
-__global__ __launch_bounds__(256) void k_ol_knn(const float4 *__restrict__ spts, int64_t n, OlHdr *hdr,
-                                                const uint32_t *__restrict__ start, const uint32_t *__restrict__ list,
-                                                const uint32_t *nlist, uint32_t *__restrict__ slow, uint32_t *nslow,
-                                                uint32_t *__restrict__ defer, float *__restrict__ dmean) {
+__device__ __forceinline__ void ol_search(const OlSearch &sr, const uint32_t *__restrict__ list, uint32_t total,
+                                          uint32_t *__restrict__ slow, uint32_t *nslow) {
+    const float4 *__restrict__ spts = sr.spts;
+    const uint32_t *__restrict__ start = sr.start;
+    const int64_t n = sr.n;
+    OlHdr *hdr = sr.hdr;
     constexpr int SIDE = 2 * RING + 1, ROWS = SIDE * SIDE, G = GR * GC;
     const float mnx = hdr->mn[0], mny = hdr->mn[1], mnz = hdr->mn[2], ih = hdr->inv_h, h = hdr->h;
     const uint32_t bx = hdr->bx, by = hdr->by, bz = hdr->bz;
     const uint32_t mx = (1u << bx) - 1u, my = (1u << by) - 1u, mz = (1u << bz) - 1u;
     const int want = n - 1 < (int64_t)K ? (int)(n - 1) : K;
-    const uint32_t total = list ? *nlist : (uint32_t)n;
     const int g = (int)(threadIdx.x % G), gr = g / GC;
     const uint32_t gc = (uint32_t)(g % GC);
     const uint32_t last = (uint32_t)n - 1u;
@@ -445,11 +459,129 @@ __global__ __launch_bounds__(256) void k_ol_knn(const float4 *__restrict__ spts,
             done = kth <= bound * bound;
         }
         if (g == 0) {
-            if (done) dmean[i] = ol_mean<K>(best, want);
-            else if (clamped || !slow) defer[atomicAdd(&hdr->ndefer, 1u)] = i;
+            if (done) sr.dmean[i] = ol_mean<K>(best, want);
+            else if (clamped || !slow) sr.defer[atomicAdd(&hdr->ndefer, 1u)] = i;
             else slow[atomicAdd(nslow, 1u)] = s;
         }
     }
+}
+
+// The third search for a long list: the cube of radius kOlShell0, then shell by shell up to
+// kOlRing3, with the stop test between (the k-th distance is within a bound iff the lanes'
+// lists hold k entries within it). Points that fill a volume settle at radius 3 or 4, whose
+// cubes have a quarter and half of radius 5's cells.
+template <int K, int GR, int GCI>
+__device__ __forceinline__ void ol_search_shells(const OlSearch &sr, const uint32_t *__restrict__ list, uint32_t total) {
+    constexpr int G = GR * GCI;
+    constexpr uint32_t GC = GCI, NB = 8;   // candidates in flight per lane
+    const float4 *__restrict__ spts = sr.spts;
+    const uint32_t *__restrict__ start = sr.start;
+    const int64_t n = sr.n;
+    OlHdr *hdr = sr.hdr;
+    const float mnx = hdr->mn[0], mny = hdr->mn[1], mnz = hdr->mn[2], ih = hdr->inv_h, h = hdr->h;
+    const uint32_t bx = hdr->bx, by = hdr->by, bz = hdr->bz;
+    const uint32_t mx = (1u << bx) - 1u, my = (1u << by) - 1u, mz = (1u << bz) - 1u;
+    const int want = n - 1 < (int64_t)K ? (int)(n - 1) : K;
+    const uint32_t last = (uint32_t)n - 1u;
+    const int l = (int)(threadIdx.x % G), gr = l / (int)GC;
+    const uint32_t gc = (uint32_t)l % GC;
+    for (uint32_t q = (blockIdx.x * 256u + threadIdx.x) / G; q < total; q += gridDim.x * (256u / G)) {
+        const float4 me = spts[list[q]];
+        const uint32_t i = __float_as_uint(me.w);
+        const float x = me.x, y = me.y, z = me.z;
+        const uint32_t cx = (uint32_t)ol_coord(x, mnx, ih), cy = (uint32_t)ol_coord(y, mny, ih), cz = (uint32_t)ol_coord(z, mnz, ih);
+        float best[K];
+#pragma unroll
+        for (int a = 0; a < K; ++a) best[a] = INFINITY;
+        auto run = [&](uint32_t a, uint32_t b) {
+            for (uint32_t j = a + gc; j < b; j += NB * GC) {
+                float4 c[NB];
+                const uint32_t left = (b - j + GC - 1) / GC;   // this lane's candidates
+#pragma unroll
+                for (uint32_t u = 0; u < NB; ++u) c[u] = spts[min(j + u * GC, last)];
+                ol_take<K, NB>(best, c, left, i, x, y, z);
+            }
+        };
+        bool done = false;
+        for (int r = kOlShell0; r <= kOlRing3 && !done; ++r) {
+            // pieces t of the shell: the side^2 rows of the cube, whole on its faces and, for
+            // the others, their first cell; then the others' last cells. The first cube: its rows.
+            const bool cube = r == kOlShell0;
+            const int side = 2 * r + 1, rows = side * side, inner = cube ? 0 : side - 2, pieces = rows + inner * inner;
+            const int rcp = 65536 / side + 1, rcp_in = inner ? 65536 / inner + 1 : 0;   // exact quotients below 256
+            struct Piece { uint32_t a, b, a2, b2; };   // one run of points, or two where it wraps
+            auto piece = [&](int t) {
+                int dy, dz, x0 = -r, x1 = r;
+                if (t < rows) {
+                    dz = (t * rcp) >> 16;
+                    dy = t - dz * side - r;
+                    dz -= r;
+                    if (!cube && max(abs(dy), abs(dz)) < r) x1 = -r;
+                } else {
+                    dz = ((t - rows) * rcp_in) >> 16;
+                    dy = t - rows - dz * inner - (r - 1);
+                    dz -= r - 1;
+                    x0 = r;
+                }
+                const uint32_t base = (((cy + (uint32_t)dy) & my) << bx) | (((cz + (uint32_t)dz) & mz) << (bx + by));
+                const uint32_t u0 = (cx + (uint32_t)x0) & mx, u1 = (cx + (uint32_t)x1) & mx;
+                const bool wrap = u0 > u1;
+                Piece p{start[base + u0], start[base + (wrap ? mx : u1) + 1u], 0u, 0u};
+                if (wrap) {
+                    p.a2 = start[base];
+                    p.b2 = start[base + u1 + 1u];
+                }
+                return p;
+            };
+            Piece p = piece(gr);
+            for (int t = gr; t < pieces; t += GR) {
+                const Piece nx = piece(t + GR < pieces ? t + GR : t);   // looked up while this one is scanned
+                run(p.a, p.b);
+                if (p.b2 > p.a2) run(p.a2, p.b2);
+                p = nx;
+            }
+            const float bound = ((float)r - kOlMargin) * h, b2 = bound * bound;
+            uint32_t c = 0;
+#pragma unroll
+            for (int a = 0; a < K; ++a) c += best[a] <= b2 ? 1u : 0u;
+#pragma unroll
+            for (int o = 1; o < G; o <<= 1) c += __shfl_xor(c, o);
+            done = c >= (uint32_t)want;
+        }
+        ol_merge_lanes<K, G>(best);
+        if (l == 0) {
+            if (done) sr.dmean[i] = ol_mean<K>(best, want);
+            else sr.defer[atomicAdd(&hdr->ndefer, 1u)] = i;
+        }
+    }
+}
+
+// The three searches. Many lanes per query are for lists that would leave the GPU idle, or
+// for rows of many points; where most of the cloud is left (a volume's points, about 1/8 per
+// cell: a row holds none or one), few lanes waste less, and the lists are long enough. The
+// whole filter over uniform points in a cube, k = 4 / 8 / 16 / 32, us, the wide forms alone
+// (radius 5 at once) and by this rule: 20,000 points 189 / 222 / 250 / 394 and 150 / 181 /
+// 214 / 346; 100,000 646 / 819 / 954 / 1691 and 339 / 466 / 730 / 1565; 400,000 1683 / 3687 /
+// 4378 / 4738 and 800 / 1120 / 1871 / 2917. Below the lines the wide forms win (3,000 points
+// 116 / 131 / 151 / 182 against 122 / 136 / 154 / 186), and where less than half of the cloud
+// is left its rows hold many points (400,000 points in clusters, k = 16: 480 against 509).
+template <int K> __global__ __launch_bounds__(256) void k_ol_knn1(OlSearch sr, uint32_t *slow, uint32_t *nslow) {
+    ol_search<K, kOlRing1, kOlR1, kOlC1>(sr, nullptr, (uint32_t)sr.n, slow, nslow);
+}
+template <int K>
+__global__ __launch_bounds__(256) void k_ol_knn2(OlSearch sr, const uint32_t *list, const uint32_t *nlist, uint32_t *slow,
+                                                 uint32_t *nslow) {
+    const uint32_t total = *nlist;
+    if (total >= kOlMany2 && total > (uint32_t)sr.n / 2u)
+        ol_search<K, kOlRing2, kOlR2Many, kOlC2Many>(sr, list, total, slow, nslow);
+    else
+        ol_search<K, kOlRing2, kOlR2, kOlC2>(sr, list, total, slow, nslow);
+}
+template <int K>
+__global__ __launch_bounds__(256) void k_ol_knn3(OlSearch sr, const uint32_t *list, const uint32_t *nlist) {
+    const uint32_t total = *nlist;
+    if (total >= kOlMany3) ol_search_shells<K, kOlR3Many, kOlC3Many>(sr, list, total);
+    else ol_search<K, kOlRing3, kOlR3, kOlC3>(sr, list, total, nullptr, nullptr);
 }
 
 // 3b. the deferred queries, one workgroup each (grid-stride over the list): each thread
@@ -743,12 +875,11 @@ static void knn_launch(const float *pts, int64_t n, int64_t stride, OlHdr *hdr, 
         const int64_t b = (n * lanes + 255) / 256;
         return dim3((unsigned)(b < most ? b : most));
     };
-    hipLaunchKernelGGL((k_ol_knn<K, kOlRing1, kOlR1, kOlC1>), grid(kOlR1 * kOlC1, (int64_t)1 << 31), dim3(256), 0, st, spts, n, hdr, start,
-                       nullptr, nullptr, slow1, hdr->nslow, defer, dmean);
-    hipLaunchKernelGGL((k_ol_knn<K, kOlRing2, kOlR2, kOlC2>), grid(kOlR2 * kOlC2, kOlListBlocks), dim3(256), 0, st, spts, n, hdr, start,
-                       slow1, hdr->nslow, slow2, hdr->nslow + 1, defer, dmean);
-    hipLaunchKernelGGL((k_ol_knn<K, kOlRing3, kOlR3, kOlC3>), grid(kOlR3 * kOlC3, kOlListBlocks), dim3(256), 0, st, spts, n, hdr, start,
-                       slow2, hdr->nslow + 1, nullptr, nullptr, defer, dmean);
+    const OlSearch sr{spts, n, hdr, start, defer, dmean};
+    hipLaunchKernelGGL((k_ol_knn1<K>), grid(kOlR1 * kOlC1, (int64_t)1 << 31), dim3(256), 0, st, sr, slow1, hdr->nslow);
+    hipLaunchKernelGGL((k_ol_knn2<K>), grid(kOlR2 * kOlC2, kOlListBlocks), dim3(256), 0, st, sr, slow1, hdr->nslow, slow2,
+                       hdr->nslow + 1);
+    hipLaunchKernelGGL((k_ol_knn3<K>), grid(kOlR3 * kOlC3, kOlListBlocks), dim3(256), 0, st, sr, slow2, hdr->nslow + 1);
     const unsigned far = (unsigned)(n < kOlFarBlocks ? n : kOlFarBlocks);
     hipLaunchKernelGGL((k_ol_knn_far<K>), dim3(far), dim3(kOlFarThreads), 0, st, spts, boxes, pts, n, stride, hdr, defer, dmean);
 }
