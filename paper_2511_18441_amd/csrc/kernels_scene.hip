@@ -41,9 +41,13 @@ __global__ __launch_bounds__(256) void k_covariance(const float *__restrict__ ls
 // serialised far from the CU, so a grid-stride loop over at most kSelectBlocks workgroups
 // bounds them. SOLO (one workgroup, up to kSelectSolo Gaussians): the workgroup stores
 // the count itself, so no launch has to zero it first (one of the two launches is the
-// larger part of such a call).
+// larger part of such a call). Where the lines lie, us per call and, of calls in a graph, on
+// the GPU: one workgroup against several, 2,048 Gaussians 7.4 and 4.0 against 9.9 and 5.1,
+// 4,096 7.2 and 5.1 against 10.1 and 5.2, 8,192 8.1 and 8.2 against 10.1 and 5.2 (it makes
+// several rounds), 16,384 14.1 against 10.2; VEC 4 against 1 on the GPU, several workgroups,
+// 8,192 Gaussians 5.2 against 4.5 (too few waves), 32,768 5.4 both, 65,536 5.7 against 6.8.
 constexpr unsigned kSelectBlocks = 1024;
-constexpr int64_t kSelectSolo = 16384;
+constexpr int64_t kSelectSolo = 4096, kSelectVec = 32768;
 
 template <typename T, int VEC> struct Pack { T v[VEC]; };
 template <typename T, int VEC> __device__ __forceinline__ Pack<T, VEC> ld_pack(const T *p) {
@@ -307,8 +311,8 @@ void launch_select(int dt, const SceneDev &sc, const CamDev &cam, const recogs_s
         return;
     }
     const int eb = dt == RECOGS_F32 ? 4 : 2;
-    const bool vec = planes_aligned(sc.means, sc.stride, 4, 16) && planes_aligned(sc.sh, sc.stride, eb, 4 * eb) &&
-                     planes_aligned(mask, 0, 1, 4);
+    const bool vec = (sc.n <= kSelectSolo || sc.n >= kSelectVec) && planes_aligned(sc.means, sc.stride, 4, 16) &&
+                     planes_aligned(sc.sh, sc.stride, eb, 4 * eb) && planes_aligned(mask, 0, 1, 4);
 #define RECOGS_SELECT(DT)                                                     \
     if (vec) select_dt<DT, 4>(sc, cam, p, mask, count, st);                   \
     else select_dt<DT, 1>(sc, cam, p, mask, count, st)
