@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "../../include/recogs.h"
+#include "host_note.hpp"
 
 namespace recogs {
 
@@ -299,14 +300,6 @@ enum : int {
     H_WORDS = 384
 };
 
-// Where the count scan also leaves the header's first eight words for the host: pinned
-// host memory, one 64-bit word each with the call's sequence number in its upper half, so
-// every word says by itself that it has arrived and no fence (a write-back of the XCD's L2)
-// is needed. words null: not wanted.
-struct HostNote {
-    uint64_t *words;
-    uint32_t seq;
-};
 __device__ __forceinline__ void leave_note(const HostNote &h, const uint32_t (&w)[8]) {
     if (!h.words) return;
 #pragma unroll
