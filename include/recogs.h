@@ -199,7 +199,8 @@ typedef struct {
     int32_t depth_bits;
     uint32_t depth_min_bits;     /* smallest float32 depth bit pattern among keys */
     int32_t last_n;
-    /* with profile_stages: milliseconds of [0] preprocess, [1] scan, [2] key-count read-back,
+    /* with profile_stages: milliseconds of [0] preprocess, [1] scan, [2] key-count read-back
+     * (until the work behind it starts; a depth pass made meanwhile counts for [3]),
      * [3] depth sort (sort_mode 0), [4] key emission, [5] key sort, [6] tile ranges,
      * [7] per-tile depth sort (sort_mode 2), [8] blend */
     float stage_ms[9];

@@ -173,7 +173,9 @@ template <typename T> T *at(const recogs_workspace *ws, size_t off) { return (T 
 // read-back returned).
 // Stage events: 0 start, then the end of [0] preprocess, [1] scan, [2] key-count read-back,
 // [3] depth sort, [4] key emission, [5] key sort, [6] tile ranges, [7] per-tile depth sort,
-// [8] blend (kStages stages, kStages + 1 events; the blend is the last).
+// [8] blend (kStages stages, kStages + 1 events; the blend is the last). A pass of the
+// depth sort enqueued before the read-back has an event of its own behind it (mode 1):
+// [2] then begins there, and [3] is that pass and what follows the read-back.
 constexpr int kStages = 9;
 constexpr int kBlendStage = kStages - 1;
 struct ProfileSet {
@@ -196,8 +198,8 @@ void harvest(recogs_workspace *ws, ProfileSet &p) {
 }
 
 struct StageTimer {
-    hipEvent_t own[kStages + 1] = {};
-    bool own_ready = false;
+    hipEvent_t own[kStages + 2] = {};   // the last: behind the early pass
+    bool own_ready = false, early = false;
     hipEvent_t *ev = nullptr;
     ProfileSet *set = nullptr;
     int mode = 0;
@@ -206,6 +208,7 @@ struct StageTimer {
         mode = m;
         st = s;
         set = nullptr;
+        early = false;
         if (mode == 0) return RECOGS_OK;
         if (mode == 1) {
             if (!own_ready) {
@@ -237,6 +240,11 @@ struct StageTimer {
         if (hipEventRecord(ev[k], st) != hipSuccess) return fail(RECOGS_ERR_HIP, "hipEventRecord failed");
         return RECOGS_OK;
     }
+    recogs_status mark_early() {
+        if (mode != 1) return RECOGS_OK;
+        early = true;
+        return mark(kStages + 1);
+    }
     // after the key-count read-back: the previous mode-2 call has completed
     void after_readback(recogs_workspace *ws) {
         if (mode != 2) return;
@@ -252,10 +260,14 @@ struct StageTimer {
         }
         if (mode != 1) return RECOGS_OK;
         if (hipEventSynchronize(ev[last]) != hipSuccess) return fail(RECOGS_ERR_HIP, "hipEventSynchronize failed");
-        for (int k = 0; k < kStages; ++k) {
+        const auto between = [&](int a, int b) {
             float ms = 0.f;
-            if (k < last && hipEventElapsedTime(&ms, ev[k], ev[k + 1]) != hipSuccess) ms = 0.f;
-            ws->stage_ms[k] = ms;
+            return hipEventElapsedTime(&ms, ev[a], ev[b]) == hipSuccess ? ms : 0.f;
+        };
+        for (int k = 0; k < kStages; ++k) ws->stage_ms[k] = k < last ? between(k, k + 1) : 0.f;
+        if (early) {
+            ws->stage_ms[2] = between(kStages + 1, 3);
+            ws->stage_ms[3] += between(2, kStages + 1);
         }
         return RECOGS_OK;
     }
@@ -626,20 +638,19 @@ recogs_status recogs_render(const recogs_scene *scene, const recogs_camera *cam,
     uint32_t *dhist = at<uint32_t>(ws, ws->off_dhist), *scount = at<uint32_t>(ws, ws->off_sort_count);
     bool early = false;
     if (note.words) {
-        if ((s = tm.mark(3)) != RECOGS_OK) return s;
         if (mode == 0 && !small) {
             launch_depth_pass(dk1, dv1, dk0, dv0, (uint32_t)n, false, hdr, dhist + kScanDigits, scount, stream);
             early = true;
             if ((s = hip_check("depth sort")) != RECOGS_OK) return s;
+            if ((s = tm.mark_early()) != RECOGS_OK) return s;
         }
         RECOGS_TRY_HIP(g_note.wait(note, stream, h));
-        tm.after_readback(ws);
     } else {
         RECOGS_TRY_HIP(hipMemcpyAsync(h, hdr, sizeof(h), hipMemcpyDeviceToHost, stream));
         RECOGS_TRY_HIP(hipStreamSynchronize(stream));
-        tm.after_readback(ws);
-        if ((s = tm.mark(3)) != RECOGS_OK) return s;
     }
+    tm.after_readback(ws);
+    if ((s = tm.mark(3)) != RECOGS_OK) return s;
     const uint64_t K = n > 0 ? ((uint64_t)h[H_K_LO] | ((uint64_t)h[H_K_HI] << 32)) : 0;
     const uint32_t V = n > 0 ? h[H_V] : 0;
     ws->num_keys = (int64_t)K;
