@@ -243,9 +243,11 @@ class Single:
 def stage_table(stages, bytes_, flops, st):
     if SORT_MODE == 0:
         # the count scan: reduce, rowscan and down (which also does the depth sort's first
-        # pass); the emission: offsets and down (its reduce is in the depth sort's last
-        # pass, and it counts the key sort's first digit, whose up pass is then skipped)
-        launches = {"key_sort": max(0, 3 * st["passes"] - 1), "depth_sort": 3 * st["dpasses"], "scan": 3, "emit": 2}
+        # pass); the emission: reduce, offsets (with a scan of the reduced sums before it
+        # past 2,048 chunks of 1,024 Gaussians) and down (which counts the key sort's first
+        # digit, whose up pass is then skipped)
+        launches = {"key_sort": max(0, 3 * st["passes"] - 1), "depth_sort": 3 * st["dpasses"], "scan": 3,
+                    "emit": 3 + (st["V"] > 2048 * 1024)}
     else:
         launches = {"key_sort": 3 * st["passes"], "depth_sort": 3 * st["dpasses"]}
     out = {}
