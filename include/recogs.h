@@ -194,7 +194,11 @@ typedef struct {
     int32_t key_bytes;           /* 8: sorted keys are (tile << 32) | depth bits; 4: tile ids */
     int32_t sorted_in_alt;       /* 1 if the sorted keys/values are in keys1/vals1 */
     int32_t sort_passes;         /* passes over the K keys */
-    int32_t depth_passes;        /* sort_mode 0: passes that the V depth keys need after the count scan's (which orders them by their low 10 depth bits); the first of them is made in any case while an eager render waits for its counts */
+    /* sort_mode 0: radix passes that the depths of the V Gaussians need behind the count
+     * scan's (which orders them by their low 10 depth bits); 2, the most, after a graph_mode
+     * render. The first is made in any case while an eager render waits for its counts.
+     * Scenes of up to 12,288 Gaussians are ordered without any of them. */
+    int32_t depth_passes;
     int32_t key_bits;            /* significant bits sorted: tile bits + depth bits */
     int32_t depth_bits;
     uint32_t depth_min_bits;     /* smallest float32 depth bit pattern among keys */

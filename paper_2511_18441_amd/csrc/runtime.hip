@@ -152,11 +152,11 @@ size_t layout(recogs_workspace *ws, int64_t n, int32_t W, int32_t H, int32_t tw,
     ws->off_sort_count = take(4 * count_words);
     // digit totals of the scan's pass and of the depth sort's two
     ws->off_dhist = take(4 * (kScanDigits + 2 * (1u << kDepthBitsMax)));
-    // zeroed each render: header; histograms; key counts of the depth-ordered emission
-    // chunks (summed by the depth sort's last pass); tile ranges
+    // key counts of the depth-ordered emission chunks
+    ws->off_esum = take(4 * (size_t)((nn + kEmitChunk - 1) / kEmitChunk));
+    // zeroed each render: header; histograms; tile ranges
     ws->off_header = take(4 * H_WORDS);
     ws->off_hist = take(4 * 256 * kMaxPasses);
-    ws->off_esum = take(4 * (size_t)((nn + kEmitChunk - 1) / kEmitChunk));
     ws->off_ranges = take(8 * (size_t)T);
     ws->scan_chunks = (size_t)scan_chunks;
     ws->sort_chunks = count_words / 256;
@@ -597,8 +597,8 @@ recogs_status recogs_render(const recogs_scene *scene, const recogs_camera *cam,
     const int mode = opts->sort_mode;
     uint32_t *dk0 = at<uint32_t>(ws, ws->off_dkeys0), *dk1 = at<uint32_t>(ws, ws->off_dkeys1);
     uint32_t *dv0 = at<uint32_t>(ws, ws->off_dvals0), *dv1 = at<uint32_t>(ws, ws->off_dvals1);
-    // the preprocess launch also zeroes the header, the digit totals, the emission sums
-    // and the tile ranges (adjacent)
+    // the preprocess launch also zeroes the header, the digit totals and the tile ranges
+    // (adjacent)
     RecolorDev rc{opts->mask, opts->M, opts->b};
     launch_preprocess(scene->storage, scene->sh_degree, make_scene(*scene), cd, rc, opts->keep_backward_state, rec, bwd, zb,
                       rect, cnt, stream, hdr, (int64_t)((ws->off_ranges - ws->off_header) / 4) + 2 * (int64_t)ntiles);
@@ -675,7 +675,7 @@ recogs_status recogs_render(const recogs_scene *scene, const recogs_camera *cam,
     ws->depth_passes = (mode == 0 && V) ? (dd.nb1 > 0) + (dd.nb2 > 0) : 0;
     ws->key_bytes = mode == 1 ? 8 : 4;
 
-    // (histograms, emission sums and tile ranges zeroed by the preprocess launch)
+    // (histograms and tile ranges zeroed by the preprocess launch)
     uint32_t *hist = at<uint32_t>(ws, ws->off_hist);
 
     uint64_t *k0 = at<uint64_t>(ws, ws->off_keys0), *k1 = at<uint64_t>(ws, ws->off_keys1);

@@ -80,3 +80,25 @@ def test_edges_of_the_chunks(R, n):
     wide = R.DeviceWorkspace(n, cam.width, cam.height, (16, 16), key_capacity=int(ws.ws.num_keys))
     assert (R.render(d, cam, wide, (16, 16), 1, sort_mode=1) == img).all()   # 64-bit keys: another sort altogether
     assert (wide.vals_sorted() == ws.vals_sorted()).all()
+
+
+# the order by counting pairs, the general chain, and more than 2,048 emission chunks
+@pytest.mark.parametrize("n", [4096, 20_000, 2_300_000])
+def test_a_workspace_of_any_content(R, n):
+    """Nothing is taken from the workspace but what the render wrote there."""
+    import torch
+    sc, cam = _scene(1 << 23, n, 3)
+    d = R.DeviceScene(sc)
+    ws = R.DeviceWorkspace(n, cam.width, cam.height, (16, 16), key_capacity=64)
+    with pytest.raises(R.RecogsError):
+        R.render(d, cam, ws, (16, 16), 1, grow=False)
+    ws = R.DeviceWorkspace(n, cam.width, cam.height, (16, 16), key_capacity=int(ws.ws.num_keys))
+    got = []
+    for fill in (0, 0xFF, 0xA5):
+        for graph in (False, True):
+            ws.mem.fill_(fill)
+            img = R.render(d, cam, ws, (16, 16), 1, grow=False, graph_mode=graph)
+            k, _ = ws.readback()
+            got.append((img, ws.vals_sorted()[:k].clone()))
+    for img, vals in got[1:]:
+        assert torch.equal(img, got[0][0]) and torch.equal(vals, got[0][1])
