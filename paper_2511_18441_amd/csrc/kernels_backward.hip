@@ -168,7 +168,7 @@ __global__ __launch_bounds__(TW *TH / PPT) void k_blend_bwd(const uint2 *__restr
     // out of the wave's bit sets, so the walk needs no test per entry
     constexpr int L = NT < 64 ? NT : 64;
     uint32_t npw = 0;
-    if constexpr (L == 64) npw = wave_max(npmax);
+    if constexpr (L == 64) npw = wave_most(npmax);
 
     const uint2 rg = ranges[tile];
     // With a thread per staged record (NT >= BATCH), the records of batch b + 1, their
@@ -371,7 +371,7 @@ __global__ __launch_bounds__((TW / 8) * (TH / (8 * PPT)) * 64) void k_blend_bwd_
         npl = max(npl, np[j]);
     }
     // the block's largest replay count: entries past it are read by no pixel here
-    npl = wave_max(npl);
+    npl = wave_most(npl);
     const uint2 rg = ranges[tile];
     float4 *wsub = sub + (size_t)region * cap + rg.x;
     ulonglong2 *wfw = fw + (size_t)region * fstride + (rg.x >> 6) + tile;
@@ -546,7 +546,7 @@ __global__ __launch_bounds__(256) void k_grad_finish(const float4 *__restrict__ 
     const uint32_t ko = i < n ? koff[i] : 0u;
     const bool use = !ovf && c > 0 && (uint64_t)ko + c <= slots;
     const uint32_t s0 = use ? ko : 0xffffffffu, s1 = use ? ko + c : 0u;
-    const uint32_t lo = wave_min(s0), hi = wave_max(s1);
+    const uint32_t lo = wave_least(s0), hi = wave_most(s1);
     float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
     for (uint32_t base = lo; base < hi; base += kPiece) {
         for (uint32_t j = lane; j < kPiece && base + j < hi; j += 64) s_slot[w][j] = gk[base + j];

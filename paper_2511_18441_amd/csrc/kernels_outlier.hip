@@ -426,7 +426,8 @@ __device__ __forceinline__ void ol_search(const OlSearch &sr, const uint32_t *__
             const uint32_t x0 = (cx - RING) & mx, x1 = (cx + RING) & mx;
             const bool wrap = x0 > x1;
             auto row = [&](int r) {   // the row's first slot (x residue 0)
-                return (((cy + (uint32_t)(r % SIDE) - RING) & my) << bx) | (((cz + (uint32_t)(r / SIDE) - RING) & mz) << (bx + by));
+                return (((cy + (uint32_t)(r % SIDE) - RING) & my) << bx) |
+                       (((cz + (uint32_t)(r / SIDE) - RING) & mz) << (bx + by));
             };
             constexpr uint32_t NB = 8;   // candidates in flight per lane
             auto run = [&](uint32_t a, uint32_t b) {
@@ -489,7 +490,8 @@ __device__ __forceinline__ void ol_search_shells(const OlSearch &sr, const uint3
         const float4 me = spts[list[q]];
         const uint32_t i = __float_as_uint(me.w);
         const float x = me.x, y = me.y, z = me.z;
-        const uint32_t cx = (uint32_t)ol_coord(x, mnx, ih), cy = (uint32_t)ol_coord(y, mny, ih), cz = (uint32_t)ol_coord(z, mnz, ih);
+        const uint32_t cx = (uint32_t)ol_coord(x, mnx, ih), cy = (uint32_t)ol_coord(y, mny, ih),
+                       cz = (uint32_t)ol_coord(z, mnz, ih);
         float best[K];
 #pragma unroll
         for (int a = 0; a < K; ++a) best[a] = INFINITY;
@@ -905,8 +907,8 @@ bool launch_outliers(const float *pts, int64_t n, int64_t stride, int k, float s
     float *bpart = (float *)(b + L.bpart);
     hipLaunchKernelGGL(k_ol_bbox, dim3(rb), dim3(256), 0, st, pts, n, stride, bpart, shist);
     const int64_t step = (n + kOlSample - 1) / kOlSample, ns = (n + step - 1) / step;
-    hipLaunchKernelGGL(k_ol_hist, dim3((unsigned)((ns + 255) / 256)), dim3(256), 0, st, pts, n, stride, ns, (uint32_t)step, bpart, rb, hdr,
-                       shist);
+    hipLaunchKernelGGL(k_ol_hist, dim3((unsigned)((ns + 255) / 256)), dim3(256), 0, st, pts, n, stride, ns, (uint32_t)step,
+                       bpart, rb, hdr, shist);
     hipLaunchKernelGGL(k_ol_setup, dim3(1), dim3(192), 0, st, shist, ns, n, (uint32_t)bits, hdr);
     hipLaunchKernelGGL(k_ol_key, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, pts, n, stride, hdr, k0, v0);
     const int alt = radix_sort_u32(k0, v0, k1, v1, (uint32_t)n, 0u, bits, (uint32_t *)(b + L.hist),
@@ -917,8 +919,8 @@ bool launch_outliers(const float *pts, int64_t n, int64_t stride, int k, float s
     uint32_t *slow2 = alt ? v0 : v1;   // the sort's other value buffer
     float4 *spts = (float4 *)(b + L.spts), *boxes = (float4 *)(b + L.boxes);
     const uint32_t sblk = (slots + 256u) / 256u;
-    hipLaunchKernelGGL(k_ol_gather, dim3(sblk + (unsigned)((n + 255) / 256)), dim3(256), 0, st, pts, n, stride, sk, sv, slots, sblk,
-                       start, spts, boxes);
+    hipLaunchKernelGGL(k_ol_gather, dim3(sblk + (unsigned)((n + 255) / 256)), dim3(256), 0, st, pts, n, stride, sk, sv, slots,
+                       sblk, start, spts, boxes);
     if (k == 4) knn_launch<4>(pts, n, stride, hdr, spts, boxes, start, slow1, slow2, defer, dmean, st);
     else if (k == 8) knn_launch<8>(pts, n, stride, hdr, spts, boxes, start, slow1, slow2, defer, dmean, st);
     else if (k == 16) knn_launch<16>(pts, n, stride, hdr, spts, boxes, start, slow1, slow2, defer, dmean, st);

@@ -302,7 +302,8 @@ __global__ __launch_bounds__(256) void k_scan_down(const uint32_t *__restrict__ 
 // kScanBits depth bits, ranked as k_radix_down ranks. 1,024 threads for a chunk of 4,096:
 // there is about one chunk per CU at 1M Gaussians, so what counts is the length of its chain
 // (loads, scan, ranking rounds, prefixes), and 16 waves take 4 rounds where 4 took 16
-// (18.3 us for 20.1 at 1M, 14.4 for 16.2 at 200k). Wave w holds entries [256 w, 256 w + 256), 64 per round; thread t digit t.
+// (18.3 us for 20.1 at 1M, 14.4 for 16.2 at 200k). Wave w holds entries
+// [256 w, 256 w + 256), 64 per round; thread t digit t.
 __global__ __launch_bounds__(1024) void k_scan_sort(const uint32_t *__restrict__ cnt, const uint32_t *__restrict__ zbits,
                                                     uint32_t *__restrict__ off, int64_t n, const uint64_t *__restrict__ pk,
                                                     const uint32_t *__restrict__ pv, uint32_t *__restrict__ dkeys,

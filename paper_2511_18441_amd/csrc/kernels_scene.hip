@@ -331,8 +331,8 @@ static void recolor_dt(const SceneDev &sc, int ncoef, void *dst, const uint8_t *
     if (copy && dst != sc.sh) {
         const unsigned gy = (unsigned)((ncoef + kCopyCoefs - 1) / kCopyCoefs);
         if (planes_aligned(sc.sh, sc.stride, Store<DT>::bytes, 16) && planes_aligned(dst, sc.stride, Store<DT>::bytes, 16))
-            hipLaunchKernelGGL((k_recolor_copy<DT, VEC>), dim3((unsigned)((sc.n + 256 * VEC - 1) / (256 * VEC)), gy), bl, 0, st, sc,
-                               ncoef, dst, mask, M, b);
+            hipLaunchKernelGGL((k_recolor_copy<DT, VEC>), dim3((unsigned)((sc.n + 256 * VEC - 1) / (256 * VEC)), gy), bl, 0, st,
+                               sc, ncoef, dst, mask, M, b);
         else
             hipLaunchKernelGGL((k_recolor_copy<DT, 1>), dim3((unsigned)((sc.n + 255) / 256), gy), bl, 0, st, sc, ncoef, dst, mask,
                                M, b);

@@ -1,14 +1,15 @@
 // Device radix sort (stable LSD, up to 8-bit digits) with 32-bit values, used for
-// the (tile, depth) order of the tile lists.
+// the (tile, depth) order of the tile lists, and below it the two passes of the depth
+// order, whose digits (up to 11 bits) follow the depth range.
 //
-// Keys are 64-bit (tile << 32) | depth_bits or 32-bit (depth bits or tile id). The
+// Keys are 64-bit (tile << 32) | depth_bits or 32-bit (tile id, or a point's slot). The
 // digits come from a view of the key that keeps only its significant bits:
 //   KV_TILE_DEPTH (64-bit): (tile << dbits) | (depth_bits - zmin)
 //   KV_SUB        (32-bit): key - zmin
 // Both views preserve the key order among the keys of one render.
 //
 // Each pass is reduce-then-scan, with no waiting between workgroups:
-//   up:      per chunk of 4,096 keys, the digit counts -> matrix [digit][chunk]
+//   up:      per chunk of 1,024 to 4,096 keys, the digit counts -> matrix [digit][chunk]
 //   rowscan: one workgroup per digit scans its row in place and writes the row total
 //   down:    per chunk, the digits' global bases come from an exclusive scan of the
 //            row totals (256 words, done by every workgroup); keys are ranked stably

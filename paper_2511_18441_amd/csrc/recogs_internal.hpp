@@ -129,16 +129,6 @@ template <typename T> __device__ __forceinline__ T wave_sum(T v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
-template <typename T> __device__ __forceinline__ T wave_min(T v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) { T w = __shfl_xor(v, o, 64); v = w < v ? w : v; }
-    return v;
-}
-template <typename T> __device__ __forceinline__ T wave_max(T v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) { T w = __shfl_xor(v, o, 64); v = w > v ? w : v; }
-    return v;
-}
 // Sum of a float over the first LANES lanes of the wave (64, or 32 / 16 when the
 // workgroup is smaller than a wave: the lanes past it do not exist and hold no
 // defined value) with DPP moves, each step one VALU add and no LDS crossbar: pairs,
@@ -350,11 +340,11 @@ struct ScanEmit {
 // scan's chunks are that pass's chunks. k_scan_reduce counts the low kScanBits bits of the
 // depth bits of each chunk's Gaussians with keys into dcnt[digit][chunk] (row stride: the
 // chunk count), a row scan makes them the chunks' digit offsets and dtot the digit
-// totals, and k_scan_down writes the chunk's (depth bits, index) pairs stably ordered
+// totals, and k_scan_sort writes the chunk's (depth bits, index) pairs stably ordered
 // by those bits (keys, vals) instead of compacted in index order.
 // 10 bits: the rest is at most 22 bits of (depth bits >> 10) - (smallest >> 10), and 16 for
 // depths within a factor of 256 (8 octaves of 2^23 values), so two further passes order
-// any scene and take 8-bit digits in nearly every one (DepthDigits).
+// any scene: 8-bit digits up to there, wider ones beyond (DepthDigits).
 constexpr int kScanBits = 10;
 constexpr uint32_t kScanDigits = 1u << kScanBits;
 struct ScanSort {
@@ -381,7 +371,11 @@ template <int SMALL, int LARGE> __device__ __forceinline__ uint32_t xcd_chunk(ui
 
 // Digits of the two passes that follow, from the depth range that the scan left in the
 // header: bits [0, nb1) and [nb1, nb1 + nb2) of (depth bits >> kScanBits) - base. A pass of
-// no bits is a stable copy.
+// no bits is a stable copy. Two passes at every range, also where their digits have 9 to 11
+// bits: captured frames, depths spread over a factor of 2, 2^8, 2^9, 2^14, 2^40, took 128, 129,
+// 131, 131, 137 us at 200k Gaussians (800 x 800) and 287, 290, 295, 296, 311 at 1M (1920 x 1080);
+// with a pass of 8 bits in the scan and three more of 8 bits behind it 148, 153, 155, 156,
+// 164 and 320, 325, 327, 329, 343.
 constexpr int kDepthBitsMax = 11;
 struct DepthDigits {
     uint32_t base;
@@ -411,7 +405,11 @@ constexpr int kScanItems = 16;                       // counts per thread of the
 constexpr int kScanChunk = 256 * kScanItems;         // counts per scan workgroup
 constexpr int kMaxPasses = 8;
 // Scenes of at most this many Gaussians get their depth order and emission offsets by
-// counting over all pairs (k_small_order) instead of by the scan and the radix passes.
+// counting over all pairs (k_small_order) instead of by the scan and the radix passes, up
+// to where that costs less than the launches it saves. Whole frames at 128 x 96, the general
+// chain against this, eager and captured, us: 2,000 Gaussians 68 / 68 against 37 / 38, 4,096
+// 73 / 75 against 42 / 43, 8,192 82 / 84 against 53 / 58, 8,300 82 / 84 against 64 / 69, 12,288
+// 89 / 91 against 77 / 83 (at 400 x 300 90 / 86 against 74 / 78). Its LDS ends there too.
 constexpr int kSmallScene = 12288;
 constexpr int kEmitItems = 4;                        // depth-ordered Gaussians per thread (emission reduce / offsets)
 constexpr int kEmitChunk = 256 * kEmitItems;         // depth-ordered Gaussians per emission workgroup

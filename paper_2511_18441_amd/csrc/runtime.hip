@@ -373,7 +373,7 @@ recogs_status check_ws(const recogs_workspace *ws, const recogs_scene *sc, const
 // The rest of a render in graph mode: no host synchronisation. Counts, the depth
 // minimum, the capacity decision and the overflow flag stay in the workspace header;
 // grids are sized for n Gaussians and key_capacity keys and workgroups past the live
-// counts return at once (sort mode 0, all 32 depth bits above the minimum).
+// counts return at once. The depth sort's digits follow the depth range in that header.
 static recogs_status render_async(const recogs_scene *scene, const recogs_camera *cam, const recogs_render_opts *opts,
                                   recogs_workspace *ws, float *image, hipStream_t stream, const CamDev &cd,
                                   StageTimer &tm) {
@@ -604,9 +604,6 @@ recogs_status recogs_render(const recogs_scene *scene, const recogs_camera *cam,
                       rect, cnt, stream, hdr, (int64_t)((ws->off_ranges - ws->off_header) / 4) + 2 * (int64_t)ntiles);
     if ((s = tm.mark(1)) != RECOGS_OK) return s;
     const HostNote note = opts->graph_mode || n == 0 ? HostNote{nullptr, 0u} : g_note.next(stream);
-    // A small scene's order by counting pairs, up to where that costs less than the launches
-    // it saves. Whole frames at 128 x 96, general chain against this: 70 / 38 us for 1,000
-    // Gaussians, 85 / 49 for 4,000, 98 / 66 for 8,192, 108 / 96 for 12,000, 121 / 126 for 16,000.
     const bool small = mode == 0 && n <= kSmallScene;
     if (small) {
         launch_small_order(cnt, zb, rect, (uint32_t)n, ws->key_capacity, off, dv0, at<uint2>(ws, ws->off_keys1), dv1,
