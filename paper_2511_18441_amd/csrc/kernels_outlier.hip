@@ -43,7 +43,7 @@ constexpr int kOlRing1 = 1, kOlRing2 = 2, kOlRing3 = 5;   // cube radii of the t
 constexpr int kOlShell0 = 3;                   // first cube of the third in shells
 constexpr int kOlR1 = 1, kOlC1 = 2, kOlR2 = 4, kOlC2 = 4, kOlR3 = 16, kOlC3 = 4;   // their lanes per query: rows x candidates
 constexpr int kOlR2Many = 2, kOlC2Many = 2, kOlR3Many = 8, kOlC3Many = 2;          // with long lists
-constexpr uint32_t kOlMany2 = 16384, kOlMany3 = 32768;
+constexpr uint32_t kOlMany2 = 16384, kOlMany2Wide = 49152, kOlMany3 = 32768;   // list lengths (Wide: k = 32)
 constexpr int kOlListBlocks = 2048;            // grid of the second and third (grid-stride over their lists)
 static_assert(2 * kOlRing3 + 1 <= 16, "one search's cells must fit in 16 slot residues per axis");
 constexpr int kOlLeaf = 64;                    // points per bounding box of the whole-cloud search
@@ -559,14 +559,16 @@ __device__ __forceinline__ void ol_search_shells(const OlSearch &sr, const uint3
 }
 
 // The three searches. Many lanes per query are for lists that would leave the GPU idle, or
-// for rows of many points; where most of the cloud is left (a volume's points, about 1/8 per
-// cell: a row holds none or one), few lanes waste less, and the lists are long enough. The
-// whole filter over uniform points in a cube, k = 4 / 8 / 16 / 32, us, the wide forms alone
-// (radius 5 at once) and by this rule: 20,000 points 189 / 222 / 250 / 394 and 150 / 181 /
-// 214 / 346; 100,000 646 / 819 / 954 / 1691 and 339 / 466 / 730 / 1565; 400,000 1683 / 3687 /
-// 4378 / 4738 and 800 / 1120 / 1871 / 2917. Below the lines the wide forms win (3,000 points
-// 116 / 131 / 151 / 182 against 122 / 136 / 154 / 186), and where less than half of the cloud
-// is left its rows hold many points (400,000 points in clusters, k = 16: 480 against 509).
+// for rows of many points; where nearly all of the cloud is left (a volume's points, about
+// 1/8 per cell: a row holds none or one), few lanes waste less, and the lists are long enough.
+// The whole filter over uniform points in a cube, k = 4 / 8 / 16 / 32, us, the wide forms alone
+// (radius 5 at once) and by this rule: 20,000 points 189 / 222 / 250 / 394 and 154 / 182 / 216 /
+// 394; 100,000 638 / 823 / 955 / 1685 and 343 / 462 / 734 / 1566; 400,000 1684 / 3686 / 4377 /
+// 4737 and 794 / 1116 / 1873 / 2910. Below the lines the wide forms win (3,000 points 116 / 131 /
+// 151 / 182 against 122 / 136 / 154 / 186; a sheet's 20,000 with k = 32 162 against 176), and
+// where a sixteenth or more of the cloud has settled its rows hold many points (a brush's
+// 47,000 points with k = 32, three quarters left: 261 against 295; 400,000 in clusters, k = 16,
+// 480 against 509).
 template <int K> __global__ __launch_bounds__(256) void k_ol_knn1(OlSearch sr, uint32_t *slow, uint32_t *nslow) {
     ol_search<K, kOlRing1, kOlR1, kOlC1>(sr, nullptr, (uint32_t)sr.n, slow, nslow);
 }
@@ -574,7 +576,7 @@ template <int K>
 __global__ __launch_bounds__(256) void k_ol_knn2(OlSearch sr, const uint32_t *list, const uint32_t *nlist, uint32_t *slow,
                                                  uint32_t *nslow) {
     const uint32_t total = *nlist;
-    if (total >= kOlMany2 && total > (uint32_t)sr.n / 2u)
+    if (total >= (K < 32 ? kOlMany2 : kOlMany2Wide) && total > (uint32_t)sr.n - (uint32_t)sr.n / 16u)
         ol_search<K, kOlRing2, kOlR2Many, kOlC2Many>(sr, list, total, slow, nslow);
     else
         ol_search<K, kOlRing2, kOlR2, kOlC2>(sr, list, total, slow, nslow);
