@@ -43,7 +43,13 @@ constexpr int kOlRing1 = 1, kOlRing2 = 2, kOlRing3 = 5;   // cube radii of the t
 constexpr int kOlShell0 = 3;                   // first cube of the third in shells
 constexpr int kOlR1 = 1, kOlC1 = 2, kOlR2 = 4, kOlC2 = 4, kOlR3 = 16, kOlC3 = 4;   // their lanes per query: rows x candidates
 constexpr int kOlR2Many = 2, kOlC2Many = 2, kOlR3Many = 8, kOlC3Many = 2;          // with long lists
-constexpr uint32_t kOlMany2 = 16384, kOlMany2Wide = 49152, kOlMany3 = 32768;   // list lengths (Wide: k = 32)
+// which lists are long: `total` queries of n points
+template <int K> __device__ __forceinline__ bool ol_many2(uint32_t total, uint32_t n) {
+    return total >= (K < 16 ? 8192u : K < 32 ? 16384u : 49152u) && total > n - n / 16u;
+}
+template <int K> __device__ __forceinline__ bool ol_many3(uint32_t total, uint32_t n) {
+    return total >= 32768u || (K < 16 && total >= 8192u + 512u * (K - 4) && total > n - n / 16u);
+}
 constexpr int kOlListBlocks = 2048;            // grid of the second and third (grid-stride over their lists)
 static_assert(2 * kOlRing3 + 1 <= 16, "one search's cells must fit in 16 slot residues per axis");
 constexpr int kOlLeaf = 64;                    // points per bounding box of the whole-cloud search
@@ -393,16 +399,17 @@ struct OlSearch {
     uint32_t *__restrict__ defer;
     float *__restrict__ dmean;
 };
+// hd: the header, read by the caller in one go with the list's length
 template <int K, int RING, int GR, int GC>
-__device__ __forceinline__ void ol_search(const OlSearch &sr, const uint32_t *__restrict__ list, uint32_t total,
+__device__ __forceinline__ void ol_search(const OlSearch &sr, const OlHdr &hd, const uint32_t *__restrict__ list, uint32_t total,
                                           uint32_t *__restrict__ slow, uint32_t *nslow) {
     const float4 *__restrict__ spts = sr.spts;
     const uint32_t *__restrict__ start = sr.start;
     const int64_t n = sr.n;
     OlHdr *hdr = sr.hdr;
     constexpr int SIDE = 2 * RING + 1, ROWS = SIDE * SIDE, G = GR * GC;
-    const float mnx = hdr->mn[0], mny = hdr->mn[1], mnz = hdr->mn[2], ih = hdr->inv_h, h = hdr->h;
-    const uint32_t bx = hdr->bx, by = hdr->by, bz = hdr->bz;
+    const float mnx = hd.mn[0], mny = hd.mn[1], mnz = hd.mn[2], ih = hd.inv_h, h = hd.h;
+    const uint32_t bx = hd.bx, by = hd.by, bz = hd.bz;
     const uint32_t mx = (1u << bx) - 1u, my = (1u << by) - 1u, mz = (1u << bz) - 1u;
     const int want = n - 1 < (int64_t)K ? (int)(n - 1) : K;
     const int g = (int)(threadIdx.x % G), gr = g / GC;
@@ -472,15 +479,16 @@ __device__ __forceinline__ void ol_search(const OlSearch &sr, const uint32_t *__
 // lists hold k entries within it). Points that fill a volume settle at radius 3 or 4, whose
 // cubes have a quarter and half of radius 5's cells.
 template <int K, int GR, int GCI>
-__device__ __forceinline__ void ol_search_shells(const OlSearch &sr, const uint32_t *__restrict__ list, uint32_t total) {
+__device__ __forceinline__ void ol_search_shells(const OlSearch &sr, const OlHdr &hd, const uint32_t *__restrict__ list,
+                                                 uint32_t total) {
     constexpr int G = GR * GCI;
     constexpr uint32_t GC = GCI, NB = 8;   // candidates in flight per lane
     const float4 *__restrict__ spts = sr.spts;
     const uint32_t *__restrict__ start = sr.start;
     const int64_t n = sr.n;
     OlHdr *hdr = sr.hdr;
-    const float mnx = hdr->mn[0], mny = hdr->mn[1], mnz = hdr->mn[2], ih = hdr->inv_h, h = hdr->h;
-    const uint32_t bx = hdr->bx, by = hdr->by, bz = hdr->bz;
+    const float mnx = hd.mn[0], mny = hd.mn[1], mnz = hd.mn[2], ih = hd.inv_h, h = hd.h;
+    const uint32_t bx = hd.bx, by = hd.by, bz = hd.bz;
     const uint32_t mx = (1u << bx) - 1u, my = (1u << by) - 1u, mz = (1u << bz) - 1u;
     const int want = n - 1 < (int64_t)K ? (int)(n - 1) : K;
     const uint32_t last = (uint32_t)n - 1u;
@@ -562,30 +570,32 @@ __device__ __forceinline__ void ol_search_shells(const OlSearch &sr, const uint3
 // for rows of many points; where nearly all of the cloud is left (a volume's points, about
 // 1/8 per cell: a row holds none or one), few lanes waste less, and the lists are long enough.
 // The whole filter over uniform points in a cube, k = 4 / 8 / 16 / 32, us, the wide forms alone
-// (radius 5 at once) and by this rule: 20,000 points 189 / 222 / 250 / 394 and 154 / 182 / 216 /
-// 394; 100,000 638 / 823 / 955 / 1685 and 343 / 462 / 734 / 1566; 400,000 1684 / 3686 / 4377 /
-// 4737 and 794 / 1116 / 1873 / 2910. Below the lines the wide forms win (3,000 points 116 / 131 /
-// 151 / 182 against 122 / 136 / 154 / 186; a sheet's 20,000 with k = 32 162 against 176), and
-// where a sixteenth or more of the cloud has settled its rows hold many points (a brush's
-// 47,000 points with k = 32, three quarters left: 261 against 295; 400,000 in clusters, k = 16,
-// 480 against 509).
-template <int K> __global__ __launch_bounds__(256) void k_ol_knn1(OlSearch sr, uint32_t *slow, uint32_t *nslow) {
-    ol_search<K, kOlRing1, kOlR1, kOlC1>(sr, nullptr, (uint32_t)sr.n, slow, nslow);
+// (radius 5 at once) and by this rule: 20,000 points 189 / 220 / 253 / 394 and 155 / 182 / 223 /
+// 394; 100,000 638 / 823 / 955 / 1685 and 334 / 456 / 725 / 1538; 400,000 1684 / 3686 / 4377 /
+// 4737 and 772 / 1074 / 1823 / 2851; over a regular grid of 14,000, k = 4 and 8, 183 / 186 and
+// 123 / 149. Below the lines the wide forms win (5,000 points, k = 4 / 8 / 16, 118 / 136 / 148
+// against 121 / 173 / 151; a plane's regular grid of 14,000 with k = 16 119 against 139; a sheet's
+// 20,000 with k = 32 162 against 176), and where a sixteenth or more of the cloud has
+// settled its rows hold many points (a brush's 47,000 points with k = 32, three quarters left:
+// 261 against 295; 400,000 in clusters, k = 16, 480 against 509).
+template <int K> __global__ __launch_bounds__(256) void k_ol_knn1(OlSearch sr, uint32_t *slow) {
+    const OlHdr hd = *sr.hdr;
+    ol_search<K, kOlRing1, kOlR1, kOlC1>(sr, hd, nullptr, (uint32_t)sr.n, slow, sr.hdr->nslow);
 }
 template <int K>
-__global__ __launch_bounds__(256) void k_ol_knn2(OlSearch sr, const uint32_t *list, const uint32_t *nlist, uint32_t *slow,
-                                                 uint32_t *nslow) {
-    const uint32_t total = *nlist;
-    if (total >= (K < 32 ? kOlMany2 : kOlMany2Wide) && total > (uint32_t)sr.n - (uint32_t)sr.n / 16u)
-        ol_search<K, kOlRing2, kOlR2Many, kOlC2Many>(sr, list, total, slow, nslow);
+__global__ __launch_bounds__(256) void k_ol_knn2(OlSearch sr, const uint32_t *list, uint32_t *slow) {
+    const OlHdr hd = *sr.hdr;
+    const uint32_t total = hd.nslow[0];
+    if (ol_many2<K>(total, (uint32_t)sr.n))
+        ol_search<K, kOlRing2, kOlR2Many, kOlC2Many>(sr, hd, list, total, slow, sr.hdr->nslow + 1);
     else
-        ol_search<K, kOlRing2, kOlR2, kOlC2>(sr, list, total, slow, nslow);
+        ol_search<K, kOlRing2, kOlR2, kOlC2>(sr, hd, list, total, slow, sr.hdr->nslow + 1);
 }
-template <int K>
-__global__ __launch_bounds__(256) void k_ol_knn3(OlSearch sr, const uint32_t *list, const uint32_t *nlist) {
-    const uint32_t total = *nlist;
-    if (total >= kOlMany3) ol_search_shells<K, kOlR3Many, kOlC3Many>(sr, list, total);
-    else ol_search<K, kOlRing3, kOlR3, kOlC3>(sr, list, total, nullptr, nullptr);
+template <int K> __global__ __launch_bounds__(256) void k_ol_knn3(OlSearch sr, const uint32_t *list) {
+    const OlHdr hd = *sr.hdr;
+    const uint32_t total = hd.nslow[1];
+    if (ol_many3<K>(total, (uint32_t)sr.n)) ol_search_shells<K, kOlR3Many, kOlC3Many>(sr, hd, list, total);
+    else ol_search<K, kOlRing3, kOlR3, kOlC3>(sr, hd, list, total, nullptr, nullptr);
 }
 
 // 3b. the deferred queries, one workgroup each (grid-stride over the list): each thread
@@ -880,10 +890,9 @@ static void knn_launch(const float *pts, int64_t n, int64_t stride, OlHdr *hdr, 
         return dim3((unsigned)(b < most ? b : most));
     };
     const OlSearch sr{spts, n, hdr, start, defer, dmean};
-    hipLaunchKernelGGL((k_ol_knn1<K>), grid(kOlR1 * kOlC1, (int64_t)1 << 31), dim3(256), 0, st, sr, slow1, hdr->nslow);
-    hipLaunchKernelGGL((k_ol_knn2<K>), grid(kOlR2 * kOlC2, kOlListBlocks), dim3(256), 0, st, sr, slow1, hdr->nslow, slow2,
-                       hdr->nslow + 1);
-    hipLaunchKernelGGL((k_ol_knn3<K>), grid(kOlR3 * kOlC3, kOlListBlocks), dim3(256), 0, st, sr, slow2, hdr->nslow + 1);
+    hipLaunchKernelGGL((k_ol_knn1<K>), grid(kOlR1 * kOlC1, (int64_t)1 << 31), dim3(256), 0, st, sr, slow1);
+    hipLaunchKernelGGL((k_ol_knn2<K>), grid(kOlR2 * kOlC2, kOlListBlocks), dim3(256), 0, st, sr, slow1, slow2);
+    hipLaunchKernelGGL((k_ol_knn3<K>), grid(kOlR3 * kOlC3, kOlListBlocks), dim3(256), 0, st, sr, slow2);
     const unsigned far = (unsigned)(n < kOlFarBlocks ? n : kOlFarBlocks);
     hipLaunchKernelGGL((k_ol_knn_far<K>), dim3(far), dim3(kOlFarThreads), 0, st, spts, boxes, pts, n, stride, hdr, defer, dmean);
 }
