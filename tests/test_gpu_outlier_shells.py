@@ -14,7 +14,7 @@ def R():
 
 
 @pytest.mark.parametrize("k", [4, 8, 16, 32])
-@pytest.mark.parametrize("kind,n", [("cube", 700), ("cube", 8_750), ("cube", 20_011), ("cube", 40_003), ("slab", 9_000), ("fading", 30_000)])
+@pytest.mark.parametrize("kind,n", [("cube", 700), ("cube", 8_750), ("cube", 20_011), ("cube", 40_003), ("cube", 60_001), ("slab", 9_000), ("fading", 30_000)])
 def test_volumes(R, kind, n, k):
     """D against a k-d tree in FP64: 4e-6 relative (a few ulps of the squared distance, half
     of that for its root, one per addition of the mean)."""
